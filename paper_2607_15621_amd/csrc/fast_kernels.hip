@@ -734,7 +734,7 @@ __global__ __launch_bounds__(256) void k_query_head(const float* __restrict__ h,
 hipError_t launch_query_head(const float* h, const TickParams& tp, const Dims& dm, const float* final_norm,
                              const QueryHead& qh, float* waypoints, hipStream_t s) {
   const int nq = dm.n_out / 2;
-  hipLaunchKernelGGL(k_query_head, dim3(tp.B), dim3(256), (size_t)nq * (dm.d + qh.hidden) * sizeof(float), s, h,
+  hipLaunchKernelGGL(k_query_head, dim3(tp.B), dim3(256), (size_t)nq * (dm.d + 256) * sizeof(float), s, h,
                      tp.S, tp.T, dm.d, dm.eps, final_norm, qh, nq, waypoints);
   return hipGetLastError();
 }

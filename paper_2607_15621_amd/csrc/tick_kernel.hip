@@ -1987,6 +1987,82 @@ __device__ __forceinline__ void poison_waypoints(const TickArgs& a, const TickPa
   for (int i = tix(); i < tp.B * dm.n_out; i += NTHR) st_dev_f(a.waypoints + i, __builtin_nanf(""));
   stores_done();
 }
+// After a head workgroup's waypoint stores: whether a failure of this launch is recorded (the same in every thread).
+__device__ __forceinline__ bool tick_failed(const TickArgs& a, TickLds& L) {
+  stores_done();
+  __syncthreads();
+  if (tix() == 0) L.ok = ld_dev(a.status) != fail_tag(a);
+  __syncthreads();
+  return !L.ok;
+}
+
+// The query head on the workgroups of XCD 0.  An agent's hidden units are split over G workgroups, G the largest power
+// of two that gives each a whole group of 64 units, at most QH_SPLIT, and has B * G workgroups there: a part is bound by
+// the latency of its weights (loaded before the wait for the last layer) and by LDS broadcasts, about 2 us per group of
+// 64, so at hidden 512 eight parts cost one group each instead of eight in a row.  Part 0 of an agent adds the others'
+// sums in order; they cross as stamped words in po, whose last reader (the last layer's R1) is done once that layer's
+// pieces are all published.  Stamps of layer n_layers are used nowhere else.  True if the waypoints must be poisoned.
+constexpr int QH_SPLIT = 8;
+__device__ __forceinline__ bool query_head_split(const TickArgs& a, const TickParams& tp, const Dims& dm, TickLds& L) {
+  const int s = uni(L.s), n = uni(L.n0), nl = dm.n_layers, nq = dm.n_out / 2, no = dm.n_out;
+  const int groups = (a.qhead.hidden + 63) / 64;
+  int G = QH_SPLIT;
+  while (G > 1 && (G > groups || tp.B * G > n)) G >>= 1;
+  const int per = (groups + G - 1) / G, g = s % G;
+  const float* h = a.hres;  // tile-major [d/16][Mp][16]
+  const uint64_t st = stamp_of(a, nl, nl);
+  const uint32_t st32 = (uint32_t)st;
+  bool wrote = false;
+  for (int b = s / G; b < tp.B; b += n / G) {
+    bool ok = true;
+    query_head_part(
+        [&](int t, int col) { return ld_dev_f(h + ((int64_t)(col >> 4) * tp.Mp + b * tp.S + t) * 16 + (col & 15)); }, tp.T,
+        nq, dm.d, dm.eps, a.final_norm, a.qhead, min(g * per, groups), min((g + 1) * per, groups),
+        [&] { return ok = wg_wait(a.f_out, dm.d / 16 * tp.rblk, stamp_of(a, nl - 1, nl), a, L); },
+        [&](int q, int c, float v) {
+          if (g == 0)
+            L.tmp[2 * q + c] = v;
+          else
+            st_dev(a.po + ((int64_t)b * G + g) * no + 2 * q + c, ((uint64_t)st32 << 32) | __float_as_uint(v));
+        },
+        reinterpret_cast<float*>(&L.u));
+    if (!ok) return true;
+    if (g == 0) {
+      const int o = tix();
+      bool got = true;
+      if (o < no) {
+        const float b2 = a.qhead.b2[o & 1];
+        const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
+        uint64_t word[QH_SPLIT];
+        for (uint32_t spin = 0;; ++spin) {
+          // every part's word loaded before any is checked (places past G load part 1's and ignore it)
+#pragma unroll
+          for (int gg = 1; gg < QH_SPLIT; ++gg)
+            word[gg] = ld_dev(a.po + ((int64_t)b * G + (gg < G ? gg : 1)) * no + o);
+          bool all = true;
+#pragma unroll
+          for (int gg = 1; gg < QH_SPLIT; ++gg) all = all && (gg >= G || (uint32_t)(word[gg] >> 32) == st32);
+          if (all) break;
+          __builtin_amdgcn_s_sleep(1);
+          if (timed_out(a, t0, spin)) {
+            st_dev(a.status, fail_tag(a));
+            got = false;
+            break;
+          }
+        }
+        float v = L.tmp[o];
+#pragma unroll
+        for (int gg = 1; gg < QH_SPLIT; ++gg)
+          if (gg < G) v += __uint_as_float((uint32_t)word[gg]);
+        if (got) st_dev_f(a.waypoints + (int64_t)b * no + o, v + b2);
+      }
+      if (!__syncthreads_and(got)) return true;
+      wrote = true;
+    }
+  }
+  return wrote && tick_failed(a, L);
+}
+
 __device__ __forceinline__ void phase_head(const TickArgs& a, const TickParams& tp, const Dims& dm, bool ok, TickLds& L) {
   const int d = dm.d, nl = dm.n_layers, T = tp.T;
   const int tid = tix(), wave = tid >> 6, lane = tid & 63;
@@ -2000,9 +2076,9 @@ __device__ __forceinline__ void phase_head(const TickArgs& a, const TickParams& 
   // the last layer, so loaded before the wait, all at once (loaded one per step of the product they were as many
   // dependent memory round trips as the product has steps)
   constexpr int HO_MAX = 16;
-  const bool regs = dm.n_out <= HO_MAX && s < tp.B;
+  const bool regs = dm.n_out <= HO_MAX && s < tp.B && dm.head_kind != 1;
   float hw0[HO_MAX], hw1[HO_MAX], g0 = 0.f, g1 = 0.f;
-  if (regs && dm.head_kind != 1) {
+  if (regs) {
     // every load unconditional (indices clamped in range, the unused values zeroed afterwards) and the dtype branch
     // outside the loop, so the loads issue back to back and cost one round trip
     const int no = dm.n_out, c0 = tid < d ? tid : d - 1, c1 = tid + NTHR < d ? tid + NTHR : d - 1;
@@ -2040,6 +2116,10 @@ __device__ __forceinline__ void phase_head(const TickArgs& a, const TickParams& 
     g0 = in0 ? g0 : 0.f;
     g1 = in1 ? g1 : 0.f;
   }
+  if (dm.head_kind == 1) {
+    if (query_head_split(a, tp, dm, L)) poison_waypoints(a, tp, dm);
+    return;
+  }
   for (int b = s; b < tp.B; b += n) {
     ok = wg_wait(a.f_out, d / 16 * tp.rblk, stamp_of(a, nl - 1, nl), a, L);  // every piece of the last layer
     if (!ok) {
@@ -2047,13 +2127,6 @@ __device__ __forceinline__ void phase_head(const TickArgs& a, const TickParams& 
       return;
     }
     const float* h = a.hres;  // tile-major [d/16][Mp][16]
-    if (dm.head_kind == 1) {
-      query_head_wg([&](int t, int col) { return ld_dev_f(h + ((int64_t)(col >> 4) * tp.Mp + b * tp.S + t) * 16 + (col & 15)); },
-                    T, dm.n_out / 2, d, dm.eps, a.final_norm, a.qhead,
-                    [&](int o, float v) { st_dev_f(a.waypoints + (int64_t)b * dm.n_out + o, v); },
-                    reinterpret_cast<float*>(&L.u));
-      continue;
-    }
     const int n0 = tid, n1 = tid + NTHR;
     auto hv = [&](int m, int col) { return ld_dev_f(h + ((int64_t)(col >> 4) * tp.Mp + m) * 16 + (col & 15)); };
     float xm0 = 0.f, xm1 = 0.f;
@@ -2123,12 +2196,7 @@ __device__ __forceinline__ void phase_head(const TickArgs& a, const TickParams& 
     }
     __syncthreads();
   }
-  if (s >= tp.B) return;
-  stores_done();
-  __syncthreads();
-  if (tix() == 0) L.ok = ld_dev(a.status) != fail_tag(a);  // one read, so the branch below is uniform
-  __syncthreads();
-  if (!L.ok) poison_waypoints(a, tp, dm);
+  if (s < tp.B && tick_failed(a, L)) poison_waypoints(a, tp, dm);
 }
 
 // ------------------------------------------------------------------------------------------ kernel

@@ -11,6 +11,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle.expert
 import synth
 from harness import Cache, Model, record, rel_err, run_forward
 from paper_2607_15621_amd import fsx
@@ -82,6 +83,36 @@ def test_paper_form_full_40_frame_shape_matches_oracle():
     record(0, rel_err(wp[0], ref), 2e-2)
     record(0, max(rel_err(hid[l, 0], ref_hid[l]) for l in range(wl.n_layers)), 2e-2,
            what="worst layer hidden, max|d| / max|ref|")
+    ex.close()
+
+
+# (path, width, hidden, outputs, expert tokens, agents): hidden units around the groups of 64 and around the eight parts an
+# agent is split into, one to eight queries, more agents than the workgroups of an XCD, widths below and not a multiple of
+# what a lane holds, and the per-op kernels' largest LDS
+HEADS = [("tick", 32, 1, 2, 1, 1), ("tick", 512, 65, 10, 10, 3), ("tick", 512, 512, 10, 10, 1), ("tick", 96, 130, 16, 8, 4),
+         ("tick", 256, 2048, 10, 10, 2), ("tick", 64, 448, 6, 5, 40), ("per-phase", 160, 129, 10, 10, 2),
+         ("generic", 1900, 48, 16, 8, 1), ("generic", 70, 200, 10, 10, 2)]
+
+
+@pytest.mark.parametrize("path,d,hidden,n_out,tokens,batch", HEADS)
+def test_query_head_at_the_edges_of_its_split(path, d, hidden, n_out, tokens, batch):
+    """The head alone: against the oracle's head on the last layer's hidden state as the GPU reports it (fp32), so only the
+    head's own sums differ.  They run over d and then `hidden` terms in fp32: 1e-4 of the largest output is over twice
+    (d + hidden) 2^-24 at the largest case, and rounding errors of a sum grow with its root."""
+    fp32 = path == "generic"
+    wl = paper_form(synth.Workload(name="head_edges", wid=520 + d + hidden, n_layers=1, d_model=d, n_heads=8, head_dim=128,
+                                   d_ffn=256, n_expert_tokens=tokens, n_frame_tokens=0, batch=batch, lengths=(3,) * batch,
+                                   dtype="f32" if fp32 else "bf16", cache_dtype="f32" if fp32 else "bf16", capacity=4,
+                                   n_out=n_out), hidden=hidden)
+    say(f"case query head {path} d={d} hidden={hidden} n_out={n_out} batch={batch}")
+    model = Model(wl)
+    ex = model.create(flags={"tick": 0, "per-phase": fsx.FLAG_MULTI_LAUNCH, "generic": fsx.FLAG_GENERIC}[path])
+    _, tok = folded_tokens(wl)
+    wp, hid = run_forward(ex, Cache(wl), tok, batch, 0, with_hidden=True)
+    h, nq = model.head_w, n_out // 2
+    for b in sorted({0, batch // 2, batch - 1}):
+        ref = oracle.expert.query_head(hid[0, b], model.final_norm, h["w1"], h["b1"], h["w2"], h["b2"], tokens, nq, wl.rms_eps)
+        record(b, rel_err(wp[b], ref), 1e-4, what="head alone, max|d| / max|ref|")
     ex.close()
 
 
