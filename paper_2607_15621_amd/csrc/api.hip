@@ -627,8 +627,7 @@ static int forward_impl(fsx_expert* ex, const fsx_cache_desc* cache, const void*
     return FSX_OK;
   }
   const int wpg = n_items >= 1024 ? 4 : 1;
-  auto kspl = [](int KB) { return KB % 8 == 0 ? 8 : (KB % 4 == 0 ? 4 : (KB % 2 == 0 ? 2 : 1)); };
-  const int ks_o = kspl(dm.A / 32), ks_d = kspl(dm.F / 32);
+  const int ks_o = gemm_split(tp.M, dm.d, dm.A), ks_d = gemm_split(tp.M, dm.d, dm.F);
 
   HIP_TRY(launch_embed(tokens, c.dtype, ex->fw[0].attn_norm, tp, dm, ex->ws, s));
   for (int l = 0; l < c.n_layers; ++l) {
@@ -901,8 +900,7 @@ extern "C" int fsx_backbone_append(fsx_backbone* bb, fsx_cache_desc* cache, cons
   tp.chunk_prefix[0] = 0;
   for (int b = 0; b < batch; ++b) tp.chunk_prefix[b + 1] = tp.chunk_prefix[b] + (int)((tp.len[b] + cr - 1) / cr) + 1;
   const int wpg = tp.n_items >= 1024 ? 4 : 1;
-  auto kspl = [](int KB) { return KB % 8 == 0 ? 8 : (KB % 4 == 0 ? 4 : (KB % 2 == 0 ? 2 : 1)); };
-  const int ks_o = kspl(dm.A / 32), ks_d = kspl(dm.F / 32);
+  const int ks_o = gemm_split(tp.M, dm.d, dm.A), ks_d = gemm_split(tp.M, dm.d, dm.F);
   HIP_TRY(launch_embed(tokens, c.dtype, ex->fw[0].attn_norm, tp, dm, ex->ws, s));
   for (int l = 0; l < c.n_layers; ++l) {
     const FastWeights& w = ex->fw[l];

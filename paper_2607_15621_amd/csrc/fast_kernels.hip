@@ -14,6 +14,7 @@
 // The head pools the first T tokens after a final RMSNorm and applies a d -> n_out map.
 
 #include <algorithm>
+#include <type_traits>
 
 #include "attn_device.h"
 #include "common.h"
@@ -147,8 +148,21 @@ struct GemmArgs {
   const float* rscale;
 };
 
+// Rotary (cos, sin) of the four rows 4 grp + i of a row tile in this lane's column of tile nt (EPI_QKV, q and k tiles;
+// loaded ahead of the epilogue, whose stores would otherwise keep each tile's loads behind those of the tile before).
 template <int EPI>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x4 s, int row0, int nt, int ks, int c, int grp) {
+__device__ __forceinline__ void load_rope(const GemmArgs& g, int row0, int nt, int c, int grp, float2 (&cs)[4]) {
+  if constexpr (EPI == EPI_QKV) {
+    const int half = g.Dh / 2, n = nt * 16 + c, nl = n % g.A, j = 8 * (nl % g.Dh / 16) + (c & 7);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      cs[i] = reinterpret_cast<const float2*>(g.rope)[(int64_t)min(row0 + 4 * grp + i, g.M - 1) * half + j];
+  }
+}
+
+template <int EPI>
+__device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x4 s, int row0, int nt, int ks, int c, int grp,
+                                              const float2 (&cs)[4]) {
   const int n = nt * 16 + c;
   if constexpr (EPI == EPI_PARTIAL) {
 #pragma unroll
@@ -185,10 +199,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x4 s, int ro
       for (int i = 0; i < 4; ++i) {
         const float other = xor8(s[i]);
         const int row = row0 + 4 * grp + i;
-        const int rrow = row < g.M ? row : 0;
-        const float cs = g.rope[((int64_t)rrow * half + j) * 2 + 0];
-        const float sn = g.rope[((int64_t)rrow * half + j) * 2 + 1];
-        const float r = c < 8 ? s[i] * cs - other * sn : s[i] * cs + other * sn;
+        const float r = c < 8 ? s[i] * cs[i].x - other * cs[i].y : s[i] * cs[i].x + other * cs[i].y;
         if (row < g.M) {
           const int64_t o = (int64_t)row * A + head * Dh + dch;
           if (sec == 0)
@@ -230,6 +241,10 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
         rsc[mt][i] = EPI != EPI_PARTIAL && g.rscale && er < g.M ? g.rscale[er] : 1.f;
       }
     }
+    float2 cs[(MT + 3) / 4][4];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+      if (mt % 4 == wave) load_rope<EPI>(g, (mg + mt) * 16, nt, c, grp, cs[mt / 4]);
     // Batches of U k-blocks of this wave: every weight block and x operand of the batch is loaded before the first
     // MFMA, so U KiB of weights per wave are in flight (one at a time leaves the stream latency-bound).
     constexpr int U = MT <= 1 ? 8 : (MT <= 2 ? 6 : (MT <= 4 ? 4 : 2));
@@ -275,146 +290,224 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
       f32x4 s = red[0][mt][lane] + red[1][mt][lane] + red[2][mt][lane] + red[3][mt][lane];
 #pragma unroll
       for (int i = 0; i < 4; ++i) s[i] *= rsc[mt][i];
-      gemm_epilogue<EPI>(g, s, (mg + mt) * 16, nt, ks, c, grp);
+      gemm_epilogue<EPI>(g, s, (mg + mt) * 16, nt, ks, c, grp, cs[mt / 4]);
     }
     __syncthreads();
   }
 }
 
-// Projection of batched rows: CT column tiles per workgroup, so each row operand loaded from L2 serves CT tiles (with
-// one tile per workgroup the rows' bytes were MT times the weights' for MT row tiles).  The 4 waves split K as in
-// k_gemm; wave w holds U batches of CT weight blocks and MT row operands, then runs CT x MT MFMA chains.
-template <int MT, int CT, int EPI>
-__global__ __launch_bounds__(256) void k_gemm_ct(GemmArgs g) {
-  __shared__ f32x4 red[4][CT][MT][WAVE];
+// Workgroup barrier without the fence that drains global loads: the callers order LDS themselves.
+__device__ __forceinline__ void wg_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// Projection of many rows.  Workgroup = 4 compute waves and 4 loader waves on MT row tiles and 4 NT column tiles; compute
+// wave w owns NT column tiles for every row, so its weights are read by nobody else and go straight from memory into a
+// register ring of RING k-blocks, while the rows pass through LDS in chunks of KCB k-blocks, three chunks deep, brought by
+// the loaders' direct loads (two loader waves per chunk, even and odd chunks in turn, so a chunk has two steps to
+// arrive).  A loader waits for its loads itself and never reads LDS; the compute waves' only loads in flight are
+// weights, so the ring keeps RING * NT KiB per wave in flight across the barriers.
+// Measured at the backbone's widths (us: q/k/v, gate/up, O + down), against workgroups whose waves split K and load the
+// rows themselves, in register batches of two k-blocks: 64 rows 48, 63, 44 -> 32, 45, 35; 512 rows 298, 400, 271 -> 62,
+// 115, 80.  Bound: the lines a CU can have in flight (see cu_bytes), at 512 rows with the MFMAs busy a third of the time;
+// one loader wave was the bound before (12 GB/s per CU), and operands read two at a time cost 40 % of the 512-row q/k/v.
+template <int MT, int NT, int KCB, int RING, int EPI>
+__global__ __launch_bounds__(512) void k_gemm_rows(GemmArgs g, int n_rb) {
+  constexpr int CPR = KCB * 4;         // 16-byte chunks of a row in one LDS chunk
+  constexpr int RPI = 64 / CPR;        // rows one direct-load instruction brings
+  constexpr int NI = MT * 16 / RPI;    // instructions per chunk
+  static_assert(CPR >= 8 && CPR <= 64 && NI % 2 == 0, "chunk size");
+  static_assert(RING % KCB == 0 || KCB % RING == 0, "chunk and ring sizes");
+  constexpr int UN = RING > KCB ? RING : KCB;  // k-blocks per unrolled pass
+  __shared__ uint4 xs[3][MT * 16 * CPR];
+  __shared__ float rs[MT * 16];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int c = lane & 15, grp = lane >> 4;
-  const int n_groups = g.N / (16 * CT);
-  const int ng = blockIdx.x % n_groups, ks = blockIdx.x / n_groups;
-  const int KB = g.K / 32;
-  const int kbs = KB / g.ksplit;
-  const int kb0 = ks * kbs, kb1 = kb0 + kbs;
-  const uint4* __restrict__ wt = g.w + (int64_t)ng * CT * KB * WAVE + lane;  // tile ct at wt + ct * KB * WAVE
-  const int n_mt = (g.M + 15) / 16;
-  for (int mg = 0; mg < n_mt; mg += MT) {
-    f32x4 acc[CT][MT];
-    const uint16_t* xr[MT];
-    bool ok[MT];
-    float rsc[MT][4];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-#pragma unroll
-      for (int ct = 0; ct < CT; ++ct) acc[ct][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-      const int row = (mg + mt) * 16 + c;
-      ok[mt] = row < g.M;
-      xr[mt] = g.x + (int64_t)(ok[mt] ? row : 0) * g.ldx + 8 * grp;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int er = (mg + mt) * 16 + 4 * grp + i;
-        rsc[mt][i] = EPI != EPI_PARTIAL && g.rscale && er < g.M ? g.rscale[er] : 1.f;
-      }
-    }
-    constexpr int U = 2;
-    int kb = kb0 + wave;
-    for (; kb + 4 * (U - 1) < kb1; kb += 4 * U) {
-      uint4 wv[U][CT], xv[U][MT];
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct) wv[u][ct] = ld_global(wt + ((int64_t)ct * KB + kb + 4 * u) * WAVE);
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-          xv[u][mt] = ok[mt] ? *reinterpret_cast<const uint4*>(xr[mt] + (kb + 4 * u) * 32) : make_uint4(0, 0, 0, 0);
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt) acc[ct][mt] = mfma_bf16(xv[u][mt], wv[u][ct], acc[ct][mt]);
-    }
-    if (kb < kb1) {  // the last, partial batch, loaded together as in k_gemm
-      uint4 wv[U][CT], xv[U][MT];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const bool in = kb + 4 * u < kb1;
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct)
-          wv[u][ct] = in ? ld_global(wt + ((int64_t)ct * KB + kb + 4 * u) * WAVE) : make_uint4(0, 0, 0, 0);
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-          xv[u][mt] = in && ok[mt] ? *reinterpret_cast<const uint4*>(xr[mt] + (kb + 4 * u) * 32) : make_uint4(0, 0, 0, 0);
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (kb + 4 * u < kb1)
-#pragma unroll
-          for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) acc[ct][mt] = mfma_bf16(xv[u][mt], wv[u][ct], acc[ct][mt]);
-    }
-#pragma unroll
-    for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) red[wave][ct][mt][lane] = acc[ct][mt];
-    __syncthreads();
-#pragma unroll
-    for (int p = 0; p < CT * MT; ++p) {
-      if (p % 4 != wave) continue;
-      const int ct = p / MT, mt = p % MT;
-      f32x4 sm = red[0][ct][mt][lane] + red[1][ct][mt][lane] + red[2][ct][mt][lane] + red[3][ct][mt][lane];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) sm[i] *= rsc[mt][i];
-      gemm_epilogue<EPI>(g, sm, (mg + mt) * 16, ng * CT + ct, ks, c, grp);
-    }
-    __syncthreads();
+  const int n_tiles = g.N / 16, KB = g.K / 32;
+  // the row blocks of one (column group, K range) run side by side on one XCD (workgroup id mod 8), sharing its L2
+  const int n_cg = (n_tiles + 4 * NT - 1) / (4 * NT);
+  const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
+  const int combo = (idx / n_rb) * 8 + xcd, rb = idx % n_rb;
+  if (combo >= n_cg * g.ksplit) return;
+  const int cg = combo % n_cg, ks = combo / n_cg;
+  const int row0 = rb * MT * 16;
+  const int kb0 = ks * KB / g.ksplit, kb1 = (ks + 1) * KB / g.ksplit;
+  const int nch = (kb1 - kb0 + KCB - 1) / KCB;
+  if (EPI != EPI_PARTIAL && threadIdx.x < MT * 16) {
+    const int row = row0 + (int)threadIdx.x;
+    rs[threadIdx.x] = g.rscale && row < g.M ? g.rscale[row] : 1.f;
   }
+  if (wave >= 4) {
+    const int par = (wave >> 1) & 1, half = wave & 1;
+    // this wave's half of chunk i of the rows, into buffer i % 3: row r's 16-byte chunk k at chunk position k ^ (r & 7)
+    // (the 16 rows of an operand read then fall in distinct banks); rows past M and k-blocks past the range repeat the
+    // last one
+    auto stage = [&](int i) {
+      uint4* buf = xs[i % 3];
+#pragma unroll 8
+      for (int qq = 0; qq < NI / 2; ++qq) {
+        const int q = 2 * qq + half;
+        const int r = q * RPI + lane / CPR, k = (lane % CPR) ^ (r & 7);
+        const int kb = min(kb0 + i * KCB + (k >> 2), kb1 - 1);
+        load_lds16<false>(g.x + (int64_t)min(row0 + r, g.M - 1) * g.ldx + kb * 32 + (k & 3) * 8, buf + q * 64);
+      }
+    };
+    if (par < nch) stage(par);
+    if (par == 0) vm_wait_all();
+    wg_barrier();
+    for (int i = 0; i + 1 < nch; ++i) {  // while chunk i is multiplied
+      if ((i & 1) == par) {
+        if (i + 2 < nch) stage(i + 2);
+      } else {
+        vm_wait_all();  // chunk i + 1
+      }
+      wg_barrier();
+    }
+    return;
+  }
+  const uint4* wt[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+    wt[t] = g.w + (int64_t)min((cg * 4 + wave) * NT + t, n_tiles - 1) * KB * WAVE + lane;
+  uint4 w[RING][NT];
+#pragma unroll
+  for (int j = 0; j < RING; ++j)
+#pragma unroll
+    for (int t = 0; t < NT; ++t) w[j][t] = ld_global(wt[t] + (int64_t)min(kb0 + j, kb1 - 1) * WAVE);
+  f32x4 acc[MT][NT];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[mt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  wg_barrier();
+  int buf = 0, kb = kb0;
+  uint4 xv[2][MT];  // the row operands of this k-block and of the next
+  auto read = [&](int jj, uint4 (&x)[MT]) {
+    const uint4* xb = &xs[buf][c * CPR + ((jj * 4 + grp) ^ (c & 7))];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) x[mt] = xb[mt * 16 * CPR];
+  };
+  read(0, xv[0]);
+  // UN k-blocks from kb on: the next k-block's operands are read (past the barrier that frees a chunk, when it is the
+  // chunk's last) before this one's products, which hide their latency; left to itself the compiler reads two operands
+  // at a time and waits for each pair.  The last pass checks each k-block against the range.
+  auto pass = [&](auto check) {
+    constexpr bool CHECK = decltype(check)::value;
+#pragma unroll
+    for (int j = 0; j < UN; ++j) {
+      if (!CHECK || kb + j < kb1) {
+        if (!CHECK || kb + j + 1 < kb1) {
+          if (j % KCB == KCB - 1) {
+            wg_barrier();
+            buf = buf == 2 ? 0 : buf + 1;
+          }
+          read((j + 1) % KCB, xv[(j + 1) & 1]);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+          for (int t = 0; t < NT; ++t) acc[mt][t] = mfma_bf16(xv[j & 1][mt], w[j % RING][t], acc[mt][t]);
+        if (!CHECK || RING < UN)
+#pragma unroll
+          for (int t = 0; t < NT; ++t) w[j % RING][t] = ld_global(wt[t] + (int64_t)min(kb + j + RING, kb1 - 1) * WAVE);
+      }
+    }
+    kb += UN;
+  };
+  static_assert(UN % 2 == 0, "operand buffers alternate");
+  while (kb + UN < kb1) pass(std::false_type());
+  pass(std::true_type());
+  float2 cs[2][NT][4];
+  auto tile_of = [&](int t) { return min((cg * 4 + wave) * NT + t, n_tiles - 1); };
+#pragma unroll
+  for (int t = 0; t < NT; ++t) load_rope<EPI>(g, row0, tile_of(t), c, grp, cs[0][t]);
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    if (mt + 1 < MT)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) load_rope<EPI>(g, row0 + (mt + 1) * 16, tile_of(t), c, grp, cs[(mt + 1) & 1][t]);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int tile = (cg * 4 + wave) * NT + t;
+      if (tile < n_tiles) {
+        f32x4 s = acc[mt][t];
+        if (EPI != EPI_PARTIAL) s *= *reinterpret_cast<const f32x4*>(&rs[mt * 16 + 4 * grp]);
+        gemm_epilogue<EPI>(g, s, row0 + mt * 16, tile, ks, c, grp, cs[mt & 1][t]);
+      }
+    }
+  }
+}
+
+template <int MT, int NT, int KCB, int RING, int EPI>
+static hipError_t launch_rows(const GemmArgs& g, hipStream_t s) {
+  const int n_rb = (g.M + MT * 16 - 1) / (MT * 16), n_cg = (g.N / 16 + 4 * NT - 1) / (4 * NT);
+  const int combos = n_cg * g.ksplit;
+  hipLaunchKernelGGL((k_gemm_rows<MT, NT, KCB, RING, EPI>), dim3((unsigned)((combos + 7) / 8 * 8 * n_rb)), dim3(512), 0, s,
+                     g, n_rb);
+  return hipGetLastError();
+}
+
+// Column tiles per compute wave for more than four row tiles (row blocks of 128), split-K ranges given: the fewest bytes
+// through a CU's L1, which bound the large products.  A CU keeps about 64 lines of 128 bytes in flight (read requests x
+// their mean latency over the CUs' cycles came to 43 and 67 in two kernels), so it loads at 64 lines per L2 latency
+// whatever the depth of the ring, and a 128 x 192 tile, for instance, waits 1,100 cycles per k-block for its 160 lines
+// against 384 cycles of products.  Workgroups run one per CU: whole rounds of 256.
+static int64_t cu_bytes(int n_mt, int tiles, int KB, int ksplit, int nt) {
+  const int64_t wgs = (int64_t)((tiles + 4 * nt - 1) / (4 * nt)) * ksplit * ((n_mt + 7) / 8);
+  return (wgs + 255) / 256 * (128 + 64 * nt) * 64 * ((KB + ksplit - 1) / ksplit);
+}
+static int pick_nt(int n_mt, int tiles, int KB, int ksplit) {
+  int best = 1;
+  for (int nt = 2; nt <= 4; ++nt)
+    if (cu_bytes(n_mt, tiles, KB, ksplit, nt) <= cu_bytes(n_mt, tiles, KB, ksplit, best)) best = nt;
+  return best;
+}
+
+// Split-K ranges of a projection [M][K] x [N][K] whose partial sums a reduction adds.  Up to four row tiles: 8 where K
+// allows (the weights bound it, and the partial sums are small).  Beyond, the count whose loads and partial sums
+// (written, read back by the reduction: twice the price of a byte from L2) are least: 512 rows of the backbone's O and
+// down take 2 x 48 us and a 19 us reduction with 8 ranges.
+int gemm_split(int M, int N, int K) {
+  const int n_mt = (M + 15) / 16, tiles = N / 16, KB = K / 32;
+  int best = KB % 8 == 0 ? 8 : (KB % 4 == 0 ? 4 : (KB % 2 == 0 ? 2 : 1));
+  if (n_mt <= 4) return best;
+  int64_t cost = INT64_MAX;
+  for (int ks = 1; ks <= 8 && ks <= KB; ks *= 2) {
+    const int64_t c = cu_bytes(n_mt, tiles, KB, ks, pick_nt(n_mt, tiles, KB, ks)) + (int64_t)ks * M * N * 8 / 256 * 2;
+    if (c < cost) {
+      best = ks;
+      cost = c;
+    }
+  }
+  return best;
 }
 
 template <int EPI>
 static hipError_t gemm_dispatch(const GemmArgs& g, hipStream_t s) {
-  const int n_mt = (g.M + 15) / 16;
-  const int groups = (n_mt + 7) / 8;
-  const int mt = (n_mt + groups - 1) / groups;
-  // several column tiles per workgroup when the rows span more than one tile and the grid still fills the chip
-  const int tiles = g.N / 16;
-  auto fills = [&](int ct) { return tiles % ct == 0 && (tiles / ct) * g.ksplit >= 256; };
-  const dim3 block(256);
-  if (mt >= 2 && mt <= 4 && fills(4)) {
-    const dim3 grid((unsigned)((tiles / 4) * g.ksplit));
-    switch (mt) {
-      case 2: hipLaunchKernelGGL((k_gemm_ct<2, 4, EPI>), grid, block, 0, s, g); break;
-      case 3: hipLaunchKernelGGL((k_gemm_ct<3, 4, EPI>), grid, block, 0, s, g); break;
-      default: hipLaunchKernelGGL((k_gemm_ct<4, 4, EPI>), grid, block, 0, s, g); break;
-    }
+  const int n_mt = (g.M + 15) / 16, tiles = g.N / 16;
+  if (n_mt == 1) {
+    // weights alone: a workgroup per column tile, its waves splitting K (gate/up of the backbone 35 us, 5.1 TB/s; the
+    // kernel for many rows 39)
+    hipLaunchKernelGGL((k_gemm<1, EPI>), dim3((unsigned)(tiles * g.ksplit)), dim3(256), 0, s, g);
     return hipGetLastError();
   }
-  if (mt >= 2 && fills(2)) {
-    const dim3 grid((unsigned)((tiles / 2) * g.ksplit));
-    switch (mt) {
-      case 2: hipLaunchKernelGGL((k_gemm_ct<2, 2, EPI>), grid, block, 0, s, g); break;
-      case 3: hipLaunchKernelGGL((k_gemm_ct<3, 2, EPI>), grid, block, 0, s, g); break;
-      case 4: hipLaunchKernelGGL((k_gemm_ct<4, 2, EPI>), grid, block, 0, s, g); break;
-      case 5: hipLaunchKernelGGL((k_gemm_ct<5, 2, EPI>), grid, block, 0, s, g); break;
-      case 6: hipLaunchKernelGGL((k_gemm_ct<6, 2, EPI>), grid, block, 0, s, g); break;
-      case 7: hipLaunchKernelGGL((k_gemm_ct<7, 2, EPI>), grid, block, 0, s, g); break;
-      default: hipLaunchKernelGGL((k_gemm_ct<8, 2, EPI>), grid, block, 0, s, g); break;
-    }
-    return hipGetLastError();
+  if (n_mt == 2) return launch_rows<2, 1, 8, 16, EPI>(g, s);
+  if (n_mt <= 4) {
+    // two column tiles per wave halve the rows' loads, as long as most CUs still have a workgroup (64 rows of the
+    // backbone: gate/up, 172 workgroups, 48 -> 45 us; q/k/v would have 96 and takes 41 against 32)
+    const int two = (tiles + 7) / 8 * g.ksplit;
+    if (two >= 160) return launch_rows<4, 2, 4, 8, EPI>(g, s);
+    return launch_rows<4, 1, 4, 16, EPI>(g, s);
   }
-  const dim3 grid((unsigned)(tiles * g.ksplit));
-  switch (mt) {
-    case 1: hipLaunchKernelGGL((k_gemm<1, EPI>), grid, block, 0, s, g); break;
-    case 2: hipLaunchKernelGGL((k_gemm<2, EPI>), grid, block, 0, s, g); break;
-    case 3: hipLaunchKernelGGL((k_gemm<3, EPI>), grid, block, 0, s, g); break;
-    case 4: hipLaunchKernelGGL((k_gemm<4, EPI>), grid, block, 0, s, g); break;
-    case 5: hipLaunchKernelGGL((k_gemm<5, EPI>), grid, block, 0, s, g); break;
-    case 6: hipLaunchKernelGGL((k_gemm<6, EPI>), grid, block, 0, s, g); break;
-    case 7: hipLaunchKernelGGL((k_gemm<7, EPI>), grid, block, 0, s, g); break;
-    default: hipLaunchKernelGGL((k_gemm<8, EPI>), grid, block, 0, s, g); break;
+  switch (pick_nt(n_mt, tiles, g.K / 32, g.ksplit)) {
+    case 1: return launch_rows<8, 1, 4, 8, EPI>(g, s);
+    case 2: return launch_rows<8, 2, 2, 8, EPI>(g, s);
+    case 3: return launch_rows<8, 3, 2, 4, EPI>(g, s);
+    default: return launch_rows<8, 4, 2, 2, EPI>(g, s);
   }
-  return hipGetLastError();
 }
 
 // After a reduction of wide rows xb holds the unscaled residual and ws.rs each row's RMSNorm scale: the

@@ -116,6 +116,8 @@ hipError_t launch_attention(const CacheView& cv, const TickParams& tp, const Dim
 // rows_into->layer (after the attention has read the old rows).
 hipError_t launch_combine(const TickParams& tp, const Dims& dm, const Workspace& ws, hipStream_t s,
                           const CacheView* rows_into = nullptr);
+// Split-K ranges (at most 8) of the output and down projections over M rows.
+int gemm_split(int M, int N, int K);
 hipError_t launch_gemm_o(const FastWeights& w, const TickParams& tp, const Dims& dm, const Workspace& ws,
                          int ksplit, hipStream_t s);
 hipError_t launch_gemm_gu(const FastWeights& w, const TickParams& tp, const Dims& dm, const Workspace& ws,

@@ -168,7 +168,7 @@ def test_backbone_full_llama_widths():
 @pytest.mark.slow
 @pytest.mark.parametrize("batch", [8, 16])
 def test_backbone_batched_llama_widths(batch):
-    # 32 or 64 new rows at LLaMA-7B widths: the projections take the several-column-tiles-per-workgroup kernel
+    # 32 or 64 new rows at LLaMA-7B widths: the projections take the kernel for many rows
     lengths = tuple(40 + 17 * b for b in range(batch))
     wl = bb_workload(760 + batch, lengths=lengths, n_new=4, capacity=320, d=4096, H=32, F=11008, n_layers=2)
     say(f"case backbone at LLaMA-7B widths, {batch} agents, 2 layers")
@@ -188,6 +188,37 @@ def test_backbone_batched_llama_widths(batch):
         record(b, rel_err(got[b][1], v_ref), TOL, what="appended values, max|d| / max|ref|")
         record(b, max(rel_err(hid[l, b], h_ref[l]) for l in range(wl.n_layers)), TOL,
                what="worst layer hidden, max|d| / max|ref|")
+    bb.bb.close()
+
+
+# (agents, new tokens, width, heads, SwiGLU): rows around the 16-row tiles, the one-tile-per-workgroup, two-, four- and
+# eight-row-tile kernels and the 128-row blocks; one to four column tiles per wave (one layer, 32 heads); ranges of
+# k-blocks that are odd or shorter than a chunk; wide rows, whose scales the projections apply
+ROWS = [(1, 16, 512, 4, 352), (1, 17, 512, 4, 352), (2, 16, 256, 4, 96), (3, 11, 512, 4, 352), (1, 64, 512, 4, 352),
+        (5, 13, 512, 4, 1024), (8, 16, 96, 4, 352), (3, 43, 512, 4, 352), (4, 50, 512, 32, 352), (8, 64, 512, 32, 11008),
+        (9, 64, 256, 32, 96), (17, 60, 2048, 16, 8192), (3, 9, 2048, 4, 96), (2, 40, 4096, 2, 160)]
+
+
+@pytest.mark.parametrize("batch,n_new,d,H,F", ROWS)
+def test_backbone_projections_over_many_rows(batch, n_new, d, H, F):
+    """Hidden state and appended rows against the oracle at the sizes where the projections change kernel or tile; the
+    first, a middle and the last agent, so the first and last row blocks."""
+    wl = bb_workload(780 + 7 * batch + n_new, lengths=(5,) * batch, n_new=n_new, capacity=n_new + 8, d=d, H=H, F=F, n_layers=1)
+    say(f"case backbone rows {batch} x {n_new}, d {d}, {H} heads, F {F}")
+    bb = BB(wl)
+    cache = Cache(wl)
+    host_tok, tok = tokens_for(wl)
+    hid = torch.full((1, batch, n_new, d), float("nan"), device="cuda")
+    bb.bb.append(cache.desc, tok, batch, n_new, hid)
+    torch.cuda.synchronize()
+    hid = hid.cpu().numpy()
+    assert np.isfinite(hid).all()
+    for b in sorted({0, batch // 2, batch - 1}):
+        k_ref, v_ref, h_ref = bb.oracle(host_tok[b], cache.oracle_rows(b), 5)
+        k_got, v_got = appended(cache, b, 5, n_new)
+        record(b, rel_err(k_got, k_ref), TOL, what="appended keys, max|d| / max|ref|")
+        record(b, rel_err(v_got, v_ref), TOL, what="appended values, max|d| / max|ref|")
+        record(b, rel_err(hid[0, b] - host_tok[b], h_ref[0] - host_tok[b]), TOL, what="layer's change, max|d| / max|ref|")
     bb.bb.close()
 
 
