@@ -280,7 +280,8 @@ static int create_impl(const fsx_expert_cfg* cfg, const fsx_layer_weights* layer
              {(void**)&ex->ws.rope, (size_t)M * Dh * 4},
              {(void**)&ex->ws.ss, (size_t)M * (d / 512 + 1) * 4},
              {(void**)&ex->ws.rs, (size_t)M * 4},
-             {(void**)&ex->ws.rcnt, (size_t)M * 4}};
+             {(void**)&ex->ws.rcnt, (size_t)M * 4},
+             {(void**)&ex->ws.acnt, (size_t)c.max_batch * H * n_tt_max * 4}};
   } else {
     parts = {{(void**)&ex->gws.h, (size_t)M * d * 4},   {(void**)&ex->gws.x, (size_t)M * d * 4},
              {(void**)&ex->gws.q, (size_t)M * A * 4},   {(void**)&ex->gws.k, (size_t)M * A * 4},
@@ -357,8 +358,10 @@ static int create_impl(const fsx_expert_cfg* cfg, const fsx_layer_weights* layer
     *p.first = q;
     q += (p.second + 255) & ~(size_t)255;
   }
-  // the per-row chunk counters of the wide-row reductions start at zero (each reduction leaves them at zero)
-  if (ex->path == 0 && !ok(hipMemsetAsync(ex->ws.rcnt, 0, (size_t)M * 4, s), "hipMemsetAsync(row counters)"))
+  // the chunk counters of the wide-row reductions and of the attention start at zero (each launch leaves them at zero)
+  if (ex->path == 0 && (!ok(hipMemsetAsync(ex->ws.rcnt, 0, (size_t)M * 4, s), "hipMemsetAsync(row counters)") ||
+                        !ok(hipMemsetAsync(ex->ws.acnt, 0, (size_t)c.max_batch * H * n_tt_max * 4, s),
+                            "hipMemsetAsync(attention counters)")))
     return cleanup(FSX_E_HIP);
   if (ex->tick) {
     // stamped words, flags, registration and status start at zero; stamps only grow
@@ -492,6 +495,25 @@ size_t static_tick_layout(const fsx_expert* ex, const TickParams& tp, char* base
 }
 }  // namespace
 
+// Split plan of the per-phase attention over the cached rows: chunks of chunk_rows rows (a multiple of 32) so that the
+// work items (chunk, head, query tile) number about 2048, eight waves per CU, and fit the workspace.
+static void plan_chunks(const fsx_expert* ex, TickParams& tp, int64_t rows) {
+  const int H = ex->cfg.n_heads;
+  const int64_t work = rows * H * tp.n_tt, target = 2048;
+  int64_t cr = std::max<int64_t>(32, ((work + target - 1) / target + 31) / 32 * 32);
+  for (;; cr *= 2) {
+    tp.chunk_prefix[0] = 0;
+    for (int b = 0; b < tp.B; ++b)
+      tp.chunk_prefix[b + 1] = tp.chunk_prefix[b] + (int)std::max<int64_t>(1, (tp.len[b] + cr - 1) / cr);
+    const int64_t items = (int64_t)tp.chunk_prefix[tp.B] * H * tp.n_tt;
+    if (items <= ex->items_max) {
+      tp.n_items = (int)items;
+      break;
+    }
+  }
+  tp.chunk_rows = (int)cr;
+}
+
 static int forward_impl(fsx_expert* ex, const fsx_cache_desc* cache, const void* tokens, int32_t batch,
                         int32_t n_frame_tokens, float* waypoints, float* hidden, void* stream, bool use_static) {
   if (!ex) return fail(FSX_E_INVALID, "expert handle is NULL");
@@ -552,26 +574,6 @@ static int forward_impl(fsx_expert* ex, const fsx_cache_desc* cache, const void*
     return FSX_OK;
   }
 
-  // split plan: chunk rows (multiple of 32) so that the work items number about 2048
-  const int target = 2048;
-  const int64_t work = rows * dm.H * tp.n_tt;
-  int64_t cr = (work + target - 1) / target;
-  cr = std::max<int64_t>(32, ((cr + 31) / 32) * 32);
-  int n_items = 0;
-  for (;;) {
-    int64_t slots = 0;
-    for (int b = 0; b < batch; ++b) slots += (tp.len[b] + cr - 1) / cr + 1;
-    const int64_t items = slots * dm.H * tp.n_tt;
-    if (items <= ex->items_max) {
-      n_items = (int)items;
-      break;
-    }
-    cr *= 2;
-  }
-  tp.chunk_rows = (int)cr;
-  tp.n_items = n_items;
-  tp.chunk_prefix[0] = 0;
-  for (int b = 0; b < batch; ++b) tp.chunk_prefix[b + 1] = tp.chunk_prefix[b] + (int)((tp.len[b] + cr - 1) / cr) + 1;
   if (ex->tick) {
     int per_cu = 0;
     HIP_TRY(tick_occupancy(cache->dtype == FSX_FP8_E4M3 ? 1 : 0, &per_cu));
@@ -626,7 +628,7 @@ static int forward_impl(fsx_expert* ex, const fsx_cache_desc* cache, const void*
     g_err.clear();
     return FSX_OK;
   }
-  const int wpg = n_items >= 1024 ? 4 : 1;
+  plan_chunks(ex, tp, rows);
   const int ks_o = gemm_split(tp.M, dm.d, dm.A), ks_d = gemm_split(tp.M, dm.d, dm.F);
 
   HIP_TRY(launch_embed(tokens, c.dtype, ex->fw[0].attn_norm, tp, dm, ex->ws, s));
@@ -634,8 +636,7 @@ static int forward_impl(fsx_expert* ex, const fsx_cache_desc* cache, const void*
     const FastWeights& w = ex->fw[l];
     cv.layer = l;
     HIP_TRY(launch_gemm_qkv(w, tp, dm, ex->ws, s, l > 0));
-    HIP_TRY(launch_attention(cv, tp, dm, ex->ws, wpg, s));
-    HIP_TRY(launch_combine(tp, dm, ex->ws, s));
+    HIP_TRY(launch_attention(cv, tp, dm, ex->ws, s));
     HIP_TRY(launch_gemm_o(w, tp, dm, ex->ws, ks_o, s));
     HIP_TRY(launch_reduce_norm(tp, dm, ex->ws, ks_o, w.ffn_norm, nullptr, s));
     HIP_TRY(launch_gemm_gu(w, tp, dm, ex->ws, s));
@@ -883,33 +884,16 @@ extern "C" int fsx_backbone_append(fsx_backbone* bb, fsx_cache_desc* cache, cons
     cv.hs = cache->capacity * cache->head_dim;
     cv.rs = cache->head_dim;
   }
-  // split plan of the attention over the cached rows (as the per-phase expert tick)
-  const int target = 2048;
-  const int64_t work = rows * dm.H * tp.n_tt;
-  int64_t cr = std::max<int64_t>(32, (((work + target - 1) / target + 31) / 32) * 32);
-  for (;;) {
-    int64_t slots = 0;
-    for (int b = 0; b < batch; ++b) slots += (tp.len[b] + cr - 1) / cr + 1;
-    if (slots * dm.H * tp.n_tt <= ex->items_max) {
-      tp.n_items = (int)(slots * dm.H * tp.n_tt);
-      break;
-    }
-    cr *= 2;
-  }
-  tp.chunk_rows = (int)cr;
-  tp.chunk_prefix[0] = 0;
-  for (int b = 0; b < batch; ++b) tp.chunk_prefix[b + 1] = tp.chunk_prefix[b] + (int)((tp.len[b] + cr - 1) / cr) + 1;
-  const int wpg = tp.n_items >= 1024 ? 4 : 1;
+  plan_chunks(ex, tp, rows);
   const int ks_o = gemm_split(tp.M, dm.d, dm.A), ks_d = gemm_split(tp.M, dm.d, dm.F);
   HIP_TRY(launch_embed(tokens, c.dtype, ex->fw[0].attn_norm, tp, dm, ex->ws, s));
   for (int l = 0; l < c.n_layers; ++l) {
     const FastWeights& w = ex->fw[l];
     cv.layer = l;
     HIP_TRY(launch_gemm_qkv(w, tp, dm, ex->ws, s, l > 0));
-    HIP_TRY(launch_attention(cv, tp, dm, ex->ws, wpg, s, true));
-    HIP_TRY(launch_combine(tp, dm, ex->ws, s, &cv));  // and the new rows, after the old ones were read
+    HIP_TRY(launch_attention(cv, tp, dm, ex->ws, s, true));
     HIP_TRY(launch_gemm_o(w, tp, dm, ex->ws, ks_o, s));
-    HIP_TRY(launch_reduce_norm(tp, dm, ex->ws, ks_o, w.ffn_norm, nullptr, s));
+    HIP_TRY(launch_reduce_norm(tp, dm, ex->ws, ks_o, w.ffn_norm, nullptr, s, &cv));  // and the new rows
     HIP_TRY(launch_gemm_gu(w, tp, dm, ex->ws, s));
     HIP_TRY(launch_gemm_down(w, tp, dm, ex->ws, ks_d, s));
     const float* gnext = l + 1 < c.n_layers ? ex->fw[l + 1].attn_norm : ex->final_norm;

@@ -230,38 +230,6 @@ __device__ __forceinline__ void load_lds16(const void* src, void* lds_base) {
   __builtin_amdgcn_global_load_lds((g_void_t*)src, (lds_void_t*)lds_base, 16, 0, COH ? 16 : 0);
 }
 
-// Plain or device-coherent access, chosen at compile time.
-template <bool COH>
-__device__ __forceinline__ uint4 ld16(const void* p) {
-  if constexpr (COH) return ld_dev16(p);
-  else return *reinterpret_cast<const uint4*>(p);
-}
-template <bool COH>
-__device__ __forceinline__ float4 ldf4(const float* p) {
-  if constexpr (COH) return ld_dev_f4(p);
-  else return *reinterpret_cast<const float4*>(p);
-}
-template <bool COH>
-__device__ __forceinline__ float ldf(const float* p) {
-  if constexpr (COH) return ld_dev_f(p);
-  else return *p;
-}
-template <bool COH>
-__device__ __forceinline__ void stf(float* p, float v) {
-  if constexpr (COH) st_dev_f(p, v);
-  else *p = v;
-}
-template <bool COH>
-__device__ __forceinline__ void stf4(float* p, float4 v) {
-  if constexpr (COH) st_dev_f4(p, v);
-  else *reinterpret_cast<float4*>(p) = v;
-}
-template <bool COH>
-__device__ __forceinline__ void st16(void* p, uint4 v) {
-  if constexpr (COH) st_dev16(p, v);
-  else *reinterpret_cast<uint4*>(p) = v;
-}
-
 __device__ __forceinline__ float block_sum(float v, float* scratch /* >= 16 floats */) {
   v = wave_sum(v);
   const int wave = threadIdx.x / WAVE, lane = threadIdx.x % WAVE;

@@ -552,21 +552,70 @@ hipError_t launch_gemm_down(const FastWeights& w, const TickParams& tp, const Di
 }
 
 // =====================================================================================================
-// Split-K joint attention (Eq. (1)): one wave = one work item (see attn_device.h); k_combine merges the
-// items of each (agent, head, query tile).
+// Split-K joint attention (Eq. (1)): one wave = one work item = (agent, head, chunk of cached rows, tile of 16 queries;
+// see attn_device.h), an agent's last chunk followed by the new tokens' own rows.  The wave that finishes last among the
+// chunks of an (agent, head, query tile) merges their states in chunk order, so no launch does; an agent of one chunk
+// writes its output at once.  Partial states cross through device-scope stores and loads, counted by a relaxed
+// device-scope atomic that the last wave resets (as k_reduce_chunks counts a row's chunks).
 // =====================================================================================================
 struct AttnArgs {
   CacheView cv;
   const float* q;
   const uint16_t* kself;
   const uint16_t* vself;
-  float* att_o;
-  float* att_ml;
-  uint16_t* attn_out;  // [M][A] bf16 (combine output)
+  float* att_o;        // [item][16][Dh] partial outputs (rows of valid queries only)
+  float* att_ml;       // [item][16][2]
+  uint32_t* acnt;      // [B * H * n_tt] chunks finished (zero between launches)
+  uint16_t* attn_out;  // [M][A] bf16
   int H, Dh, A;
   int causal;          // the own rows are masked causally (new token t sees own rows 0..t)
-  int write_rows;      // combine launch: also store the new rows (kself/vself) into the cache rings (cv)
 };
+
+// Log-sum-exp merge of the nslot states at items it0, it0 + step, ... (in that order) by one wave: lane l takes query
+// t0 + l / 16, channels 8 (l % 16) .. + 7; the states are loaded RB at a time, every load before any use.
+__device__ __forceinline__ void merge_items(const AttnArgs& a, int64_t it0, int64_t step, int nslot, int rows, int lane,
+                                            uint16_t* dst /* query 0, channel 0 */) {
+  constexpr int RB = 8;
+  const int d0 = 8 * (lane & 15);
+  for (int t0 = 0; t0 < rows; t0 += 4) {
+    const int t = min(t0 + (lane >> 4), rows - 1);
+    float M = -INFINITY, L = 0.f, acc[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) acc[k] = 0.f;
+    for (int s0 = 0; s0 < nslot; s0 += RB) {
+      float m[RB], l[RB];
+      float4 x0[RB], x1[RB];
+#pragma unroll
+      for (int j = 0; j < RB; ++j) {
+        const int64_t item = it0 + step * min(s0 + j, nslot - 1);
+        m[j] = ld_dev_f(a.att_ml + item * 32 + 2 * t);
+        l[j] = ld_dev_f(a.att_ml + item * 32 + 2 * t + 1);
+        const float* po = a.att_o + (item * 16 + t) * a.Dh + d0;
+        x0[j] = ld_dev_f4(po);
+        x1[j] = ld_dev_f4(po + 4);
+      }
+#pragma unroll
+      for (int j = 0; j < RB; ++j) {
+        if (s0 + j < nslot) {
+          const float mn = fmaxf(M, m[j]);
+          const float fa = M == -INFINITY ? 0.f : exp2f(M - mn), fb = exp2f(m[j] - mn);
+          L = L * fa + l[j] * fb;
+          acc[0] = acc[0] * fa + x0[j].x * fb; acc[1] = acc[1] * fa + x0[j].y * fb;
+          acc[2] = acc[2] * fa + x0[j].z * fb; acc[3] = acc[3] * fa + x0[j].w * fb;
+          acc[4] = acc[4] * fa + x1[j].x * fb; acc[5] = acc[5] * fa + x1[j].y * fb;
+          acc[6] = acc[6] * fa + x1[j].z * fb; acc[7] = acc[7] * fa + x1[j].w * fb;
+          M = mn;
+        }
+      }
+    }
+    if (t0 + (lane >> 4) < rows) {
+      const float inv = 1.0f / L;
+      *reinterpret_cast<uint4*>(dst + (int64_t)t * a.A + d0) =
+          make_uint4(pack_bf16x2(acc[0] * inv, acc[1] * inv), pack_bf16x2(acc[2] * inv, acc[3] * inv),
+                     pack_bf16x2(acc[4] * inv, acc[5] * inv), pack_bf16x2(acc[6] * inv, acc[7] * inv));
+    }
+  }
+}
 
 template <int KT>
 __global__ __launch_bounds__(256) void k_attention(AttnArgs a, TickParams tp) {
@@ -579,23 +628,19 @@ __global__ __launch_bounds__(256) void k_attention(AttnArgs a, TickParams tp) {
   const int cs = rest / a.H;
   int b = 0;
   while (b + 1 < tp.B && tp.chunk_prefix[b + 1] <= cs) ++b;
-  const int cidx = cs - tp.chunk_prefix[b];
-  const int nch = tp.chunk_prefix[b + 1] - tp.chunk_prefix[b] - 1;
-  const int grp = lane >> 4;
-  const int t = tt * 16 + (lane & 15);
+  const int first = tp.chunk_prefix[b], nslot = tp.chunk_prefix[b + 1] - first, cidx = cs - first;
+  const int grp = lane >> 4, c = lane & 15;
+  const int t = tt * 16 + c, rows = min(16, tp.S - tt * 16);
   const bool tv = t < tp.S;
   const int64_t qrow = ((int64_t)b * tp.S + (tv ? t : 0)) * a.A + (int64_t)h * a.Dh;
-  float* out_o = a.att_o + (int64_t)item * 16 * a.Dh;
-  float* out_ml = a.att_ml + (int64_t)item * 32;
   uint4 qf[4];
-  if (cidx == nch) {  // the expert's own rows (bf16)
-    load_q_frag<0, false>(a.q, qrow, tv, grp, qf);
-    const int64_t off = ((int64_t)b * tp.S * a.A + (int64_t)h * a.Dh) * 2;
-    attn_rows<0, false, false, false>((const char*)a.kself + off, (const char*)a.vself + off, (int64_t)a.A * 2, 0, 0, 0, tp.S, qf,
-                        1.f, 1.f, lane, out_o, out_ml, a.Dh, a.causal ? tt * 16 : 1 << 30);
-  } else {
-    const int i0 = cidx * tp.chunk_rows;
-    const int i1 = min(i0 + tp.chunk_rows, tp.len[b]);
+  AttnState st;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) st.o[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+  st.m = -INFINITY;
+  st.l = 0.f;
+  const int i0 = cidx * tp.chunk_rows, i1 = min(i0 + tp.chunk_rows, tp.len[b]);
+  if (i0 < i1) {
     constexpr int ES = KT == 0 ? 2 : 1;
     // ring slot 0 of (agent, layer, head); slots are a.cv.rs elements apart
     const int64_t off = cache_head_base(a.cv, b, a.cv.layer, h) * ES;
@@ -605,18 +650,65 @@ __global__ __launch_bounds__(256) void k_attention(AttnArgs a, TickParams tp) {
       ks = a.cv.k_scale[si];
       vs = a.cv.v_scale[si];
     }
-    load_q_frag<KT, false>(a.q, qrow, tv, grp, qf);
-    attn_rows<KT, true, false, false>((const char*)a.cv.k + off, (const char*)a.cv.v + off, a.cv.rs * ES, tp.start[b],
-                        a.cv.cap, i0, i1, qf, ks, vs, lane, out_o, out_ml, a.Dh);
+    load_q_frag<KT>(a.q, qrow, tv, grp, qf);
+    // chunks start at rows equal modulo the chunk, rings are often a power of two: every item would stream addresses
+    // equal modulo that, so each starts at a tile of its own
+    const int n = (i1 - i0 + 31) / 32;
+    attn_rows<KT, true>((const char*)a.cv.k + off, (const char*)a.cv.v + off, a.cv.rs * ES, tp.start[b], a.cv.cap, i0, i1,
+                        (int)((5u * h + 3u * b + cidx) % (unsigned)n), qf, ks, lane, st);
+    if (KT == 1)
+#pragma unroll
+      for (int k = 0; k < 8; ++k) st.o[k] *= vs;
   }
+  if (cidx == nslot - 1) {  // the new tokens' own rows (bf16)
+    if (KT == 1 || i0 >= i1) load_q_frag<0>(a.q, qrow, tv, grp, qf);
+    const int64_t off = ((int64_t)b * tp.S * a.A + (int64_t)h * a.Dh) * 2;
+    attn_rows<0, false>((const char*)a.kself + off, (const char*)a.vself + off, (int64_t)a.A * 2, 0, 0, 0, tp.S, 0, qf, 1.f,
+                        lane, st, a.causal ? tt * 16 : 1 << 30);
+  }
+  const float lt = rows_sum(st.l);
+  uint16_t* out = a.attn_out + ((int64_t)b * tp.S + tt * 16) * a.A + (int64_t)h * a.Dh;
+  if (nslot == 1) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float inv = 1.0f / col_pick(lt, grp, i);
+      if (4 * grp + i < rows)
+        *reinterpret_cast<uint4*>(out + (int64_t)(4 * grp + i) * a.A + 8 * c) =
+            make_uint4(pack_bf16x2(st.o[0][i] * inv, st.o[1][i] * inv), pack_bf16x2(st.o[2][i] * inv, st.o[3][i] * inv),
+                       pack_bf16x2(st.o[4][i] * inv, st.o[5][i] * inv), pack_bf16x2(st.o[6][i] * inv, st.o[7][i] * inv));
+    }
+    return;
+  }
+  if (grp == 0 && c < rows) {
+    st_dev_f(a.att_ml + (int64_t)item * 32 + 2 * c, st.m);
+    st_dev_f(a.att_ml + (int64_t)item * 32 + 2 * c + 1, lt);
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (4 * grp + i < rows) {
+      float* dst = a.att_o + ((int64_t)item * 16 + 4 * grp + i) * a.Dh + 8 * c;
+      st_dev_f4(dst, make_float4(st.o[0][i], st.o[1][i], st.o[2][i], st.o[3][i]));
+      st_dev_f4(dst + 4, make_float4(st.o[4][i], st.o[5][i], st.o[6][i], st.o[7][i]));
+    }
+  }
+  stores_done();
+  uint32_t* cnt = a.acnt + ((int64_t)b * a.H + h) * tp.n_tt + tt;
+  uint32_t done = 0;
+  if (lane == 0) done = __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  done = (uint32_t)__builtin_amdgcn_readfirstlane((int)done);
+  if (done != (uint32_t)(nslot - 1)) return;
+  if (lane == 0) __hip_atomic_store(cnt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const int64_t step = (int64_t)a.H * tp.n_tt;  // items between two chunks of the agent
+  merge_items(a, (int64_t)first * step + (int64_t)h * tp.n_tt + tt, step, nslot, rows, lane, out);
 }
 
 hipError_t launch_attention(const CacheView& cv, const TickParams& tp, const Dims& dm, const Workspace& ws,
-                            int waves_per_wg, hipStream_t s, bool causal) {
+                            hipStream_t s, bool causal) {
   AttnArgs a{};
   a.cv = cv; a.q = ws.q; a.kself = ws.kself; a.vself = ws.vself; a.att_o = ws.att_o; a.att_ml = ws.att_ml;
-  a.H = dm.H; a.Dh = dm.Dh; a.A = dm.A; a.causal = causal ? 1 : 0;
-  const dim3 grid((unsigned)((tp.n_items + waves_per_wg - 1) / waves_per_wg)), block(64 * waves_per_wg);
+  a.acnt = ws.acnt; a.attn_out = ws.attn; a.H = dm.H; a.Dh = dm.Dh; a.A = dm.A; a.causal = causal ? 1 : 0;
+  const int wpg = tp.n_items >= 1024 ? 4 : 1;
+  const dim3 grid((unsigned)((tp.n_items + wpg - 1) / wpg)), block(64 * wpg);
   if (cv.dtype == FSX_FP8_E4M3)
     hipLaunchKernelGGL(k_attention<1>, grid, block, 0, s, a, tp);
   else
@@ -624,76 +716,33 @@ hipError_t launch_attention(const CacheView& cv, const TickParams& tp, const Dim
   return hipGetLastError();
 }
 
-// Log-sum-exp merge of the work items of one (agent, head, query tile), in item order.
-__device__ __forceinline__ void write_row_chunk(const CacheView& cv, const uint16_t* ks, const uint16_t* vs,
-                                                const TickParams& tp, int64_t i);
-
-// Workgroups past the B * H * n_tt merges (when a.write_rows is set) store the layer's new rows into the cache.
-__global__ __launch_bounds__(256) void k_combine(AttnArgs a, TickParams tp) {
-  const int n_merge = tp.B * a.H * tp.n_tt;
-  if ((int)blockIdx.x >= n_merge) {
-    write_row_chunk(a.cv, a.kself, a.vself, tp, (int64_t)(blockIdx.x - n_merge) * blockDim.x + threadIdx.x);
-    return;
-  }
-  const int tt = blockIdx.x % tp.n_tt;
-  const int rest = blockIdx.x / tp.n_tt;
-  const int h = rest % a.H;
-  const int b = rest / a.H;
-  const int first = tp.chunk_prefix[b], nslot = tp.chunk_prefix[b + 1] - first;
-  const int t = threadIdx.x >> 4, d0 = (threadIdx.x & 15) * 8;
-  float M = -INFINITY;
-  for (int sl = 0; sl < nslot; ++sl) {
-    const int64_t item = ((int64_t)(first + sl) * a.H + h) * tp.n_tt + tt;
-    M = fmaxf(M, a.att_ml[item * 32 + t * 2]);
-  }
-  float L = 0.f, acc[8];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) acc[k] = 0.f;
-  for (int sl = 0; sl < nslot; ++sl) {
-    const int64_t item = ((int64_t)(first + sl) * a.H + h) * tp.n_tt + tt;
-    const float w = exp2f(a.att_ml[item * 32 + t * 2] - M);
-    L += a.att_ml[item * 32 + t * 2 + 1] * w;
-    const float4* po = reinterpret_cast<const float4*>(a.att_o + (item * 16 + t) * a.Dh + d0);
-    const float4 x0 = po[0], x1 = po[1];
-    acc[0] += x0.x * w; acc[1] += x0.y * w; acc[2] += x0.z * w; acc[3] += x0.w * w;
-    acc[4] += x1.x * w; acc[5] += x1.y * w; acc[6] += x1.z * w; acc[7] += x1.w * w;
-  }
-  const int tok = tt * 16 + t;
-  if (tok < tp.S) {
-    const float inv = 1.0f / L;
-    const uint4 out = make_uint4(pack_bf16x2(acc[0] * inv, acc[1] * inv), pack_bf16x2(acc[2] * inv, acc[3] * inv),
-                                 pack_bf16x2(acc[4] * inv, acc[5] * inv), pack_bf16x2(acc[6] * inv, acc[7] * inv));
-    *reinterpret_cast<uint4*>(a.attn_out + ((int64_t)b * tp.S + tok) * a.A + (int64_t)h * a.Dh + d0) = out;
-  }
-}
-
-hipError_t launch_combine(const TickParams& tp, const Dims& dm, const Workspace& ws, hipStream_t s,
-                          const CacheView* rows_into) {
-  AttnArgs a{};
-  a.att_o = ws.att_o; a.att_ml = ws.att_ml; a.attn_out = ws.attn; a.H = dm.H; a.Dh = dm.Dh; a.A = dm.A;
-  int64_t blocks = (int64_t)tp.B * dm.H * tp.n_tt;
-  if (rows_into) {
-    a.cv = *rows_into;
-    a.kself = ws.kself;
-    a.vself = ws.vself;
-    a.write_rows = 1;
-    blocks += ((int64_t)tp.B * tp.S * rows_into->H * (rows_into->Dh / 8) + 255) / 256;
-  }
-  hipLaunchKernelGGL(k_combine, dim3((unsigned)blocks), dim3(256), 0, s, a, tp);
-  return hipGetLastError();
-}
+// The layer's new rows (kself / vself) into the cache rings, by the workgroups of a reduction past its own (the first
+// launch after the attention has read the old rows, which a full ring overwrites).
+struct RowsInto {
+  CacheView cv;
+  const uint16_t* ks;
+  const uint16_t* vs;
+  int32_t B, n;
+  int64_t first[FSX_MAX_BATCH];  // ring slot of each agent's first new row
+};
+__device__ __forceinline__ void write_row_chunk(const RowsInto& w, int64_t i);
 
 // =====================================================================================================
 // h += sum of split-K partials (fixed order), optional copy to the per-layer hidden output, then
 // x = bf16(h / rms(h)) for the next projection (whose packed weights carry the norm gain).  One workgroup
 // per token row.
 // =====================================================================================================
+template <bool ROWS>
 __global__ __launch_bounds__(256) void k_reduce_norm(float* __restrict__ h, const float* __restrict__ part,
                                                      uint16_t* __restrict__ xb, int M, int d, int ksplit,
                                                      const float* __restrict__ gain, float eps,
-                                                     float* __restrict__ hidden) {
+                                                     float* __restrict__ hidden, RowsInto w) {
   __shared__ float red[16];
   const int m = blockIdx.x;
+  if (ROWS && m >= M) {
+    write_row_chunk(w, (int64_t)(m - M) * blockDim.x + threadIdx.x);
+    return;
+  }
   float ss = 0.f;
   for (int n = threadIdx.x; n < d; n += blockDim.x) {
     const int64_t idx = (int64_t)m * d + n;
@@ -717,13 +766,18 @@ __global__ __launch_bounds__(256) void k_reduce_norm(float* __restrict__ h, cons
 // partials, xb = bf16(h) unscaled, and the chunk's sum of squares to ss[m][chunk]; the last chunk of the row forms
 // the row's RMSNorm scale, which the next projection applies to its products, so no launch forms the normalised
 // input.
+template <bool ROWS>
 __global__ __launch_bounds__(RN_CHUNK / 4) void k_reduce_chunks(float* __restrict__ h, const float* __restrict__ part,
                                                                 int M, int d, int ksplit, float* __restrict__ ss,
                                                                 uint16_t* __restrict__ xb, float* __restrict__ hidden,
                                                                 float* __restrict__ rs, uint32_t* __restrict__ rcnt,
-                                                                float eps) {
+                                                                float eps, RowsInto w) {
   __shared__ float red[16];
   const int nch = d / RN_CHUNK, m = blockIdx.x / nch, ch = blockIdx.x % nch;
+  if (ROWS && m >= M) {
+    write_row_chunk(w, (int64_t)(blockIdx.x - M * nch) * blockDim.x + threadIdx.x);
+    return;
+  }
   // thread t: the 4 columns ch * RN_CHUNK + 4t .. + 3, 16-byte loads (every partial's load issued before any add)
   const int64_t idx = (int64_t)m * d + ch * RN_CHUNK + 4 * threadIdx.x;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -770,15 +824,25 @@ __global__ __launch_bounds__(RN_CHUNK / 4) void k_reduce_chunks(float* __restric
 }
 
 hipError_t launch_reduce_norm(const TickParams& tp, const Dims& dm, const Workspace& ws, int ksplit,
-                              const float* gain, float* hidden_layer, hipStream_t s) {
-  if (wide_rows(dm)) {
-    const int nch = dm.d / RN_CHUNK;
-    hipLaunchKernelGGL(k_reduce_chunks, dim3(tp.M * nch), dim3(RN_CHUNK / 4), 0, s, ws.h, (const float*)ws.part, tp.M, dm.d,
-                       ksplit, ws.ss, ws.xb, hidden_layer, ws.rs, ws.rcnt, dm.eps);
-    return hipGetLastError();
+                              const float* gain, float* hidden_layer, hipStream_t s, const CacheView* rows_into) {
+  RowsInto w{};
+  int64_t chunks = 0;
+  if (rows_into) {
+    w.cv = *rows_into; w.ks = ws.kself; w.vs = ws.vself; w.B = tp.B; w.n = tp.S;
+    for (int b = 0; b < tp.B; ++b) w.first[b] = (tp.start[b] + tp.len[b]) % rows_into->cap;
+    chunks = (int64_t)tp.B * tp.S * rows_into->H * (rows_into->Dh / 8);
   }
-  hipLaunchKernelGGL(k_reduce_norm, dim3(tp.M), dim3(256), 0, s, ws.h, (const float*)ws.part, ws.xb, tp.M, dm.d,
-                     ksplit, gain, dm.eps, hidden_layer);
+  const int nt = wide_rows(dm) ? RN_CHUNK / 4 : 256, own = wide_rows(dm) ? tp.M * (dm.d / RN_CHUNK) : tp.M;
+  const dim3 grid((unsigned)(own + (chunks + nt - 1) / nt)), block(nt);
+  if (wide_rows(dm)) {
+    const auto fn = rows_into ? k_reduce_chunks<true> : k_reduce_chunks<false>;
+    hipLaunchKernelGGL(fn, grid, block, 0, s, ws.h, (const float*)ws.part, tp.M, dm.d, ksplit, ws.ss, ws.xb, hidden_layer,
+                       ws.rs, ws.rcnt, dm.eps, w);
+  } else {
+    const auto fn = rows_into ? k_reduce_norm<true> : k_reduce_norm<false>;
+    hipLaunchKernelGGL(fn, grid, block, 0, s, ws.h, (const float*)ws.part, ws.xb, tp.M, dm.d, ksplit, gain, dm.eps,
+                       hidden_layer, w);
+  }
   return hipGetLastError();
 }
 
@@ -1001,28 +1065,24 @@ hipError_t launch_append_quantize(const fsx_cache_desc& c, const void* k_rows, c
   return hipGetLastError();
 }
 
-// The new tokens' rotated keys and values of one layer (kself / vself, bf16 [B*n][H*Dh]) written into that layer's
-// ring slots (first[b] + t) mod cap, bf16 copies or fp8 codes against the cache's scales.  Thread i handles 8
-// channels of one head row.
-// Chunk i (8 elements) of the new rows [B][n][H][Dh] (kself/vself layout, row b * n + t) into ring slot
-// (start + len + t) mod capacity of (agent b, layer cv.layer, head h): a bf16 copy, or E4M3 codes with the cache's
-// per-(agent, layer, head) scales.  Runs after the attention that read the old rows (a full ring overwrites its
-// oldest rows).
-__device__ __forceinline__ void write_row_chunk(const CacheView& cv, const uint16_t* ks, const uint16_t* vs,
-                                                const TickParams& tp, int64_t i) {
-  const int cpr = cv.Dh / 8, A = cv.H * cv.Dh, n = tp.S;
-  const int64_t total = (int64_t)tp.B * n * cv.H * cpr;
+// Chunk i (8 elements) of the new rows [B][n][H][Dh] (kself / vself: bf16, rotated; row b * n + t) into ring slot
+// (first[b] + t) mod capacity of (agent b, layer cv.layer, head h): a bf16 copy, or E4M3 codes with the cache's
+// per-(agent, layer, head) scales.
+__device__ __forceinline__ void write_row_chunk(const RowsInto& w, int64_t i) {
+  const CacheView& cv = w.cv;
+  const int cpr = cv.Dh / 8, A = cv.H * cv.Dh, n = w.n;
+  const int64_t total = (int64_t)w.B * n * cv.H * cpr;
   if (i >= total) return;
   const int ch = (int)(i % cpr);
   int64_t r = i / cpr;
   const int h = (int)(r % cv.H);
   const int64_t m = r / cv.H;  // token row b * n + t
   const int b = (int)(m / n), t = (int)(m % n);
-  int64_t slot = (tp.start[b] + tp.len[b]) % cv.cap + t;
+  int64_t slot = w.first[b] + t;
   if (slot >= cv.cap) slot -= cv.cap;
   const int64_t dst = cache_head_base(cv, b, cv.layer, h) + slot * cv.rs + 8 * ch;
   const int64_t src = m * A + (int64_t)h * cv.Dh + 8 * ch;
-  const uint4 kv = *reinterpret_cast<const uint4*>(ks + src), vv = *reinterpret_cast<const uint4*>(vs + src);
+  const uint4 kv = *reinterpret_cast<const uint4*>(w.ks + src), vv = *reinterpret_cast<const uint4*>(w.vs + src);
   if (cv.dtype == FSX_FP8_E4M3) {
     const int64_t si = cache_scale_index(cv, b, cv.layer, h);
     const float sk = cv.k_scale[si], sv = cv.v_scale[si];

@@ -20,7 +20,7 @@ struct TickParams {
   int64_t pos[FSX_MAX_BATCH];                 // rotary position of token 0
   int64_t start[FSX_MAX_BATCH];               // ring slot of the oldest valid row
   int32_t len[FSX_MAX_BATCH];                 // valid cache rows
-  int32_t chunk_prefix[FSX_MAX_BATCH + 1];    // per-phase path: chunk slots before agent b (ceil(len/chunk_rows) + 1 each)
+  int32_t chunk_prefix[FSX_MAX_BATCH + 1];    // per-phase path: chunks before agent b (max(1, ceil(len / chunk_rows)) each)
   // tick kernel attention: agents in the order order[0..B-1]; the k-th weighs seg_w[k] work tiles per head
   // (its 32-row cache tiles, then the 32-row tiles of the expert's own rows), seg_p[k] = seg_w[0] + ... +
   // seg_w[k-1]; partial-state slots of XCD X
@@ -90,6 +90,7 @@ struct Workspace {
   float* ss;         // [M][d/512] per-chunk sums of squares (wide rows)
   float* rs;         // [M] RMSNorm scale of each row (wide rows)
   uint32_t* rcnt;    // [M] chunks of the row reduced so far (wide rows; zero between launches)
+  uint32_t* acnt;    // [B*H*n_tt] attention chunks finished (zero between launches)
 };
 
 struct Dims {
@@ -109,13 +110,9 @@ hipError_t launch_embed(const void* tokens, int tok_dtype, const float* g0, cons
 // projection applies the RMSNorm row scales from the chunk sums of squares.
 hipError_t launch_gemm_qkv(const FastWeights& w, const TickParams& tp, const Dims& dm, const Workspace& ws,
                            hipStream_t s, bool after_reduction);
+// The attention of every (agent, head), its work items (tp.chunk_prefix, tp.n_items) merged.
 hipError_t launch_attention(const CacheView& cv, const TickParams& tp, const Dims& dm, const Workspace& ws,
-                            int waves_per_wg, hipStream_t s, bool causal = false);
-// Merges the attention's partial states; with rows_into, the same launch also stores the layer's new rows
-// (ws.kself / ws.vself, B agents x S tokens) into ring slots (start + len + t) mod capacity of cache layer
-// rows_into->layer (after the attention has read the old rows).
-hipError_t launch_combine(const TickParams& tp, const Dims& dm, const Workspace& ws, hipStream_t s,
-                          const CacheView* rows_into = nullptr);
+                            hipStream_t s, bool causal = false);
 // Split-K ranges (at most 8) of the output and down projections over M rows.
 int gemm_split(int M, int N, int K);
 hipError_t launch_gemm_o(const FastWeights& w, const TickParams& tp, const Dims& dm, const Workspace& ws,
@@ -124,8 +121,10 @@ hipError_t launch_gemm_gu(const FastWeights& w, const TickParams& tp, const Dims
                           hipStream_t s);
 hipError_t launch_gemm_down(const FastWeights& w, const TickParams& tp, const Dims& dm, const Workspace& ws,
                             int ksplit, hipStream_t s);
+// With rows_into, the same launch also stores the layer's new rows (ws.kself / ws.vself, B agents x S tokens) into ring
+// slots (start + len + t) mod capacity of cache layer rows_into->layer (after the attention has read the old rows).
 hipError_t launch_reduce_norm(const TickParams& tp, const Dims& dm, const Workspace& ws, int ksplit,
-                              const float* gain, float* hidden_layer, hipStream_t s);
+                              const float* gain, float* hidden_layer, hipStream_t s, const CacheView* rows_into = nullptr);
 hipError_t launch_head(const TickParams& tp, const Dims& dm, const Workspace& ws, const float* final_norm,
                        const void* head_w, int head_dtype, float* waypoints, hipStream_t s);
 // The two-layer query head of every agent from a row-major residual h [M][d] (both per-op paths).

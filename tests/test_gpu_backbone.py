@@ -222,6 +222,32 @@ def test_backbone_projections_over_many_rows(batch, n_new, d, H, F):
     bb.bb.close()
 
 
+@pytest.mark.parametrize("cache_dtype", ["bf16", "fp8"])
+def test_backbone_attention_chunks_and_their_merge(cache_dtype):
+    """Agents of no chunk (own rows alone), one, two and over eight chunks of cached rows, partial tiles, two query tiles; the
+    chunks' last wave merges them and resets their count, so a second call gives the same bits."""
+    lengths = (0, 1, 32, 33, 300, 1000)
+    wl = bb_workload(770, lengths=lengths, n_new=20, capacity=1024, cache_dtype=cache_dtype)
+    say(f"case backbone attention chunks {cache_dtype}")
+    bb = BB(wl)
+    cache = Cache(wl, starts=(0, 1023, 5, 1000, 900, 37))
+    state = [x.copy() for x in (cache.desc.start, cache.desc.len, cache.desc.pos)]
+    host_tok, tok = tokens_for(wl)
+    hid = [torch.full((wl.n_layers, wl.batch, 20, wl.d_model), float("nan"), device="cuda") for _ in range(2)]
+    for h in hid:
+        for dst, src in zip((cache.desc.start, cache.desc.len, cache.desc.pos), state):
+            dst[:] = src
+        bb.bb.append(cache.desc, tok, wl.batch, 20, h)
+    torch.cuda.synchronize()
+    assert torch.equal(hid[0], hid[1])
+    got = hid[0].cpu().numpy()
+    for b in range(wl.batch):
+        _, _, h_ref = bb.oracle(host_tok[b], cache.oracle_rows(b, decoded=True), lengths[b])
+        record(b, max(rel_err(got[l, b], h_ref[l]) for l in range(wl.n_layers)), TOL,
+               what="worst layer hidden, max|d| / max|ref|")
+    bb.bb.close()
+
+
 def test_expert_tick_over_rows_the_backbone_appended():
     # producer -> consumer: the backbone extends the cache, then the expert reads it
     wl = bb_workload(740, lengths=(100, 64), n_new=4, capacity=128, d=512, H=16, F=1024)
