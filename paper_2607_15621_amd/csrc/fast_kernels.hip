@@ -303,18 +303,18 @@ __device__ __forceinline__ void wg_barrier() {
   asm volatile("" ::: "memory");
 }
 
-// Projection of many rows.  Workgroup = 4 compute waves and 4 loader waves on MT row tiles and 4 NT column tiles; compute
+// Projection of many rows.  Workgroup = CW compute waves and 4 loader waves on MT row tiles and CW NT column tiles; compute
 // wave w owns NT column tiles for every row, so its weights are read by nobody else and go straight from memory into a
 // register ring of RING k-blocks, while the rows pass through LDS in chunks of KCB k-blocks, three chunks deep, brought by
 // the loaders' direct loads (two loader waves per chunk, even and odd chunks in turn, so a chunk has two steps to
 // arrive).  A loader waits for its loads itself and never reads LDS; the compute waves' only loads in flight are
 // weights, so the ring keeps RING * NT KiB per wave in flight across the barriers.
 // Measured at the backbone's widths (us: q/k/v, gate/up, O + down), against workgroups whose waves split K and load the
-// rows themselves, in register batches of two k-blocks: 64 rows 48, 63, 44 -> 32, 45, 35; 512 rows 298, 400, 271 -> 62,
-// 115, 80.  Bound: the lines a CU can have in flight (see cu_bytes), at 512 rows with the MFMAs busy a third of the time;
+// rows themselves, in register batches of two k-blocks: 64 rows 48, 63, 44 -> 28, 38, 35; 512 rows 298, 400, 271 -> 62,
+// 115, 80.  Bound: the lines a CU can have in flight (see cu_cost), at 512 rows with the MFMAs busy a third of the time;
 // one loader wave was the bound before (12 GB/s per CU), and operands read two at a time cost 40 % of the 512-row q/k/v.
-template <int MT, int NT, int KCB, int RING, int EPI>
-__global__ __launch_bounds__(512) void k_gemm_rows(GemmArgs g, int n_rb) {
+template <int MT, int NT, int KCB, int RING, int EPI, int CW>
+__global__ __launch_bounds__((CW + 4) * 64) void k_gemm_rows(GemmArgs g, int n_rb) {
   constexpr int CPR = KCB * 4;         // 16-byte chunks of a row in one LDS chunk
   constexpr int RPI = 64 / CPR;        // rows one direct-load instruction brings
   constexpr int NI = MT * 16 / RPI;    // instructions per chunk
@@ -327,7 +327,7 @@ __global__ __launch_bounds__(512) void k_gemm_rows(GemmArgs g, int n_rb) {
   const int c = lane & 15, grp = lane >> 4;
   const int n_tiles = g.N / 16, KB = g.K / 32;
   // the row blocks of one (column group, K range) run side by side on one XCD (workgroup id mod 8), sharing its L2
-  const int n_cg = (n_tiles + 4 * NT - 1) / (4 * NT);
+  const int n_cg = (n_tiles + CW * NT - 1) / (CW * NT);
   const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
   const int combo = (idx / n_rb) * 8 + xcd, rb = idx % n_rb;
   if (combo >= n_cg * g.ksplit) return;
@@ -339,8 +339,8 @@ __global__ __launch_bounds__(512) void k_gemm_rows(GemmArgs g, int n_rb) {
     const int row = row0 + (int)threadIdx.x;
     rs[threadIdx.x] = g.rscale && row < g.M ? g.rscale[row] : 1.f;
   }
-  if (wave >= 4) {
-    const int par = (wave >> 1) & 1, half = wave & 1;
+  if (wave >= CW) {
+    const int par = ((wave - CW) >> 1) & 1, half = (wave - CW) & 1;
     // this wave's half of chunk i of the rows, into buffer i % 3: row r's 16-byte chunk k at chunk position k ^ (r & 7)
     // (the 16 rows of an operand read then fall in distinct banks); rows past M and k-blocks past the range repeat the
     // last one
@@ -370,7 +370,7 @@ __global__ __launch_bounds__(512) void k_gemm_rows(GemmArgs g, int n_rb) {
   const uint4* wt[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t)
-    wt[t] = g.w + (int64_t)min((cg * 4 + wave) * NT + t, n_tiles - 1) * KB * WAVE + lane;
+    wt[t] = g.w + (int64_t)min((cg * CW + wave) * NT + t, n_tiles - 1) * KB * WAVE + lane;
   uint4 w[RING][NT];
 #pragma unroll
   for (int j = 0; j < RING; ++j)
@@ -421,7 +421,7 @@ __global__ __launch_bounds__(512) void k_gemm_rows(GemmArgs g, int n_rb) {
   while (kb + UN < kb1) pass(std::false_type());
   pass(std::true_type());
   float2 cs[2][NT][4];
-  auto tile_of = [&](int t) { return min((cg * 4 + wave) * NT + t, n_tiles - 1); };
+  auto tile_of = [&](int t) { return min((cg * CW + wave) * NT + t, n_tiles - 1); };
 #pragma unroll
   for (int t = 0; t < NT; ++t) load_rope<EPI>(g, row0, tile_of(t), c, grp, cs[0][t]);
 #pragma unroll
@@ -431,7 +431,7 @@ __global__ __launch_bounds__(512) void k_gemm_rows(GemmArgs g, int n_rb) {
       for (int t = 0; t < NT; ++t) load_rope<EPI>(g, row0 + (mt + 1) * 16, tile_of(t), c, grp, cs[(mt + 1) & 1][t]);
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-      const int tile = (cg * 4 + wave) * NT + t;
+      const int tile = (cg * CW + wave) * NT + t;
       if (tile < n_tiles) {
         f32x4 s = acc[mt][t];
         if (EPI != EPI_PARTIAL) s *= *reinterpret_cast<const f32x4*>(&rs[mt * 16 + 4 * grp]);
@@ -441,42 +441,46 @@ __global__ __launch_bounds__(512) void k_gemm_rows(GemmArgs g, int n_rb) {
   }
 }
 
-template <int MT, int NT, int KCB, int RING, int EPI>
+template <int MT, int NT, int KCB, int RING, int EPI, int CW = 4>
 static hipError_t launch_rows(const GemmArgs& g, hipStream_t s) {
-  const int n_rb = (g.M + MT * 16 - 1) / (MT * 16), n_cg = (g.N / 16 + 4 * NT - 1) / (4 * NT);
+  const int n_rb = (g.M + MT * 16 - 1) / (MT * 16), n_cg = (g.N / 16 + CW * NT - 1) / (CW * NT);
   const int combos = n_cg * g.ksplit;
-  hipLaunchKernelGGL((k_gemm_rows<MT, NT, KCB, RING, EPI>), dim3((unsigned)((combos + 7) / 8 * 8 * n_rb)), dim3(512), 0, s,
+  hipLaunchKernelGGL((k_gemm_rows<MT, NT, KCB, RING, EPI, CW>), dim3((unsigned)((combos + 7) / 8 * 8 * n_rb)), dim3((CW + 4) * 64), 0, s,
                      g, n_rb);
   return hipGetLastError();
 }
 
-// Column tiles per compute wave for more than four row tiles (row blocks of 128), split-K ranges given: the fewest bytes
-// through a CU's L1, which bound the large products.  A CU keeps about 64 lines of 128 bytes in flight (read requests x
-// their mean latency over the CUs' cycles came to 43 and 67 in two kernels), so it loads at 64 lines per L2 latency
-// whatever the depth of the ring, and a 128 x 192 tile, for instance, waits 1,100 cycles per k-block for its 160 lines
-// against 384 cycles of products.  Workgroups run one per CU: whole rounds of 256.
-static int64_t cu_bytes(int n_mt, int tiles, int KB, int ksplit, int nt) {
-  const int64_t wgs = (int64_t)((tiles + 4 * nt - 1) / (4 * nt)) * ksplit * ((n_mt + 7) / 8);
-  return (wgs + 255) / 256 * (128 + 64 * nt) * 64 * ((KB + ksplit - 1) / ksplit);
+// What a projection's workgroups cost a CU, in 128-byte lines weighted by how long each keeps its place: a CU has about
+// 64 lines in flight (read requests x their mean latency over the CUs' cycles came to 43 to 67 in these kernels),
+// whatever the depth of the ring, so its time goes with the lines it loads: 8 per column tile and k-block for the
+// weights, 8 per row tile for the rows, in whole rounds of 256 workgroups.  A line of weights from memory takes about
+// three times as long as one of the rows from L2; with several row blocks all but one find the weights in L2.
+static int64_t cu_cost(int n_rb, int mt, int tiles, int KB, int ksplit, int tpw) {
+  const int64_t wgs = (int64_t)((tiles + tpw - 1) / tpw) * ksplit * n_rb;
+  return (wgs + 255) / 256 * (8 * tpw * (n_rb > 1 ? 1 : 3) + 8 * mt) * ((KB + ksplit - 1) / ksplit);
 }
-static int pick_nt(int n_mt, int tiles, int KB, int ksplit) {
-  int best = 1;
-  for (int nt = 2; nt <= 4; ++nt)
-    if (cu_bytes(n_mt, tiles, KB, ksplit, nt) <= cu_bytes(n_mt, tiles, KB, ksplit, best)) best = nt;
+// Column tiles per workgroup: the cheapest of what the kernels are built for.
+static int pick_tiles(int n_mt, int tiles, int KB, int ksplit) {
+  const int n_rb = (n_mt + 7) / 8, mt = n_mt > 4 ? 8 : (n_mt > 2 ? 4 : 2);
+  static constexpr int one[] = {3, 4, 6, 8}, many[] = {4, 8, 12, 16};
+  const int* opt = n_rb > 1 ? many : one;
+  int best = opt[0];
+  for (int i = 1; i < 4; ++i)
+    if (cu_cost(n_rb, mt, tiles, KB, ksplit, opt[i]) <= cu_cost(n_rb, mt, tiles, KB, ksplit, best)) best = opt[i];
   return best;
 }
 
-// Split-K ranges of a projection [M][K] x [N][K] whose partial sums a reduction adds.  Up to four row tiles: 8 where K
-// allows (the weights bound it, and the partial sums are small).  Beyond, the count whose loads and partial sums
-// (written, read back by the reduction: twice the price of a byte from L2) are least: 512 rows of the backbone's O and
-// down take 2 x 48 us and a 19 us reduction with 8 ranges.
+// Split-K ranges of a projection [M][K] x [N][K] whose partial sums a reduction adds.  One row block: 8 where K allows (the
+// weights bound it, and the partial sums are small).  Beyond, the count whose loads and partial sums (written, and read
+// back by the reduction: twice the price of a line from L2) are least: 512 rows of the backbone's O and down and their
+// reductions take 110 + 39 us with 8 ranges, 80 + 29 with the 2 and 4 chosen.
 int gemm_split(int M, int N, int K) {
-  const int n_mt = (M + 15) / 16, tiles = N / 16, KB = K / 32;
+  const int n_mt = (M + 15) / 16, n_rb = (n_mt + 7) / 8, tiles = N / 16, KB = K / 32;
   int best = KB % 8 == 0 ? 8 : (KB % 4 == 0 ? 4 : (KB % 2 == 0 ? 2 : 1));
-  if (n_mt <= 4) return best;
+  if (n_rb == 1) return best;
   int64_t cost = INT64_MAX;
   for (int ks = 1; ks <= 8 && ks <= KB; ks *= 2) {
-    const int64_t c = cu_bytes(n_mt, tiles, KB, ks, pick_nt(n_mt, tiles, KB, ks)) + (int64_t)ks * M * N * 8 / 256 * 2;
+    const int64_t c = cu_cost(n_rb, 8, tiles, KB, ks, pick_tiles(n_mt, tiles, KB, ks)) + (int64_t)ks * M * N * 8 / 128 / 256 * 2;
     if (c < cost) {
       best = ks;
       cost = c;
@@ -494,19 +498,32 @@ static hipError_t gemm_dispatch(const GemmArgs& g, hipStream_t s) {
     hipLaunchKernelGGL((k_gemm<1, EPI>), dim3((unsigned)(tiles * g.ksplit)), dim3(256), 0, s, g);
     return hipGetLastError();
   }
-  if (n_mt == 2) return launch_rows<2, 1, 8, 16, EPI>(g, s);
-  if (n_mt <= 4) {
-    // two column tiles per wave halve the rows' loads, as long as most CUs still have a workgroup (64 rows of the
-    // backbone: gate/up, 172 workgroups, 48 -> 45 us; q/k/v would have 96 and takes 41 against 32)
-    const int two = (tiles + 7) / 8 * g.ksplit;
-    if (two >= 160) return launch_rows<4, 2, 4, 8, EPI>(g, s);
-    return launch_rows<4, 1, 4, 16, EPI>(g, s);
+  // 64 rows of the backbone, us by tiles per workgroup (3, 4, 6, 8): gate/up 46, 49, 38, 45; q/k/v 28, 31, 35, 40; O and
+  // down together 45, 39, 42, 35
+  const int tpw = pick_tiles(n_mt, tiles, g.K / 32, g.ksplit);
+  if (n_mt <= 2) {
+    switch (tpw) {
+      case 3: return launch_rows<2, 1, 8, 16, EPI, 3>(g, s);
+      case 4: return launch_rows<2, 1, 8, 16, EPI, 4>(g, s);
+      case 6: return launch_rows<2, 1, 8, 8, EPI, 6>(g, s);
+      default: return launch_rows<2, 2, 8, 8, EPI, 4>(g, s);
+    }
   }
-  switch (pick_nt(n_mt, tiles, g.K / 32, g.ksplit)) {
-    case 1: return launch_rows<8, 1, 4, 8, EPI>(g, s);
-    case 2: return launch_rows<8, 2, 2, 8, EPI>(g, s);
-    case 3: return launch_rows<8, 3, 2, 4, EPI>(g, s);
-    default: return launch_rows<8, 4, 2, 2, EPI>(g, s);
+  if (n_mt <= 4) {
+    switch (tpw) {
+      case 3: return launch_rows<4, 1, 4, 16, EPI, 3>(g, s);
+      case 4: return launch_rows<4, 1, 4, 16, EPI, 4>(g, s);
+      case 6: return launch_rows<4, 1, 4, 8, EPI, 6>(g, s);
+      default: return launch_rows<4, 2, 4, 8, EPI, 4>(g, s);
+    }
+  }
+  switch (tpw) {
+    case 3: return launch_rows<8, 1, 4, 8, EPI, 3>(g, s);
+    case 4: return launch_rows<8, 1, 4, 8, EPI, 4>(g, s);
+    case 6: return launch_rows<8, 1, 4, 8, EPI, 6>(g, s);
+    case 8: return launch_rows<8, 2, 2, 8, EPI, 4>(g, s);
+    case 12: return launch_rows<8, 3, 2, 4, EPI, 4>(g, s);
+    default: return launch_rows<8, 4, 2, 2, EPI, 4>(g, s);
   }
 }
 
