@@ -283,10 +283,9 @@ static int create_impl(const fsx_expert_cfg* cfg, const fsx_layer_weights* layer
              {(void**)&ex->ws.rcnt, (size_t)M * 4},
              {(void**)&ex->ws.acnt, (size_t)c.max_batch * H * n_tt_max * 4}};
   } else {
-    parts = {{(void**)&ex->gws.h, (size_t)M * d * 4},   {(void**)&ex->gws.x, (size_t)M * d * 4},
-             {(void**)&ex->gws.q, (size_t)M * A * 4},   {(void**)&ex->gws.k, (size_t)M * A * 4},
-             {(void**)&ex->gws.v, (size_t)M * A * 4},   {(void**)&ex->gws.attn, (size_t)M * A * 4},
-             {(void**)&ex->gws.g, (size_t)M * F * 4},   {(void**)&ex->gws.u, (size_t)M * F * 4},
+    parts = {{(void**)&ex->gws.h, (size_t)M * d * 4},   {(void**)&ex->gws.q, (size_t)M * A * 4},
+             {(void**)&ex->gws.k, (size_t)M * A * 4},   {(void**)&ex->gws.v, (size_t)M * A * 4},
+             {(void**)&ex->gws.attn, (size_t)M * A * 4}, {(void**)&ex->gws.g, (size_t)M * F * 4},
              {(void**)&ex->gws.rope, (size_t)M * Dh * 4}};
   }
   const int nflag_attn = c.max_batch * H;

@@ -871,29 +871,7 @@ __global__ __launch_bounds__(256) void k_head(const float* __restrict__ h, int S
                                               const float* __restrict__ gfin, const void* __restrict__ w,
                                               int wdtype, int n_out, float* __restrict__ wp) {
   extern __shared__ float xm[];
-  __shared__ float red[16];
-  const int b = blockIdx.x;
-  for (int n = threadIdx.x; n < d; n += blockDim.x) xm[n] = 0.f;
-  for (int t = 0; t < T; ++t) {
-    const float* hr = h + ((int64_t)b * S + t) * d;
-    float ss = 0.f;
-    for (int n = threadIdx.x; n < d; n += blockDim.x) ss += hr[n] * hr[n];
-    ss = block_sum(ss, red);
-    const float r = 1.0f / sqrtf(ss / (float)d + eps);
-    for (int n = threadIdx.x; n < d; n += blockDim.x) xm[n] += hr[n] * r * gfin[n];
-  }
-  __syncthreads();
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
-  for (int o = wave; o < n_out; o += nw) {
-    float acc = 0.f;
-    for (int n = lane; n < d; n += WAVE) {
-      const float wv = wdtype == FSX_BF16 ? bf16_to_f32(((const uint16_t*)w)[(int64_t)o * d + n])
-                                          : ((const float*)w)[(int64_t)o * d + n];
-      acc += xm[n] * wv;
-    }
-    acc = wave_sum(acc);
-    if (lane == 0) wp[(int64_t)b * n_out + o] = acc / (float)T;
-  }
+  mean_head_wg(h, S, T, d, eps, gfin, w, wdtype, n_out, wp, xm);
 }
 
 __global__ __launch_bounds__(256) void k_query_head(const float* __restrict__ h, int S, int T, int d, float eps,

@@ -23,6 +23,44 @@ __device__ __forceinline__ float qh_weight(const void* w, int wdtype, int64_t i)
   return wdtype == FSX_BF16 ? bf16_to_f32(reinterpret_cast<const uint16_t*>(w)[i]) : reinterpret_cast<const float*>(w)[i];
 }
 
+// The mean-pool head of one agent of the per-op paths (blockIdx.x; residual h [M][d], S rows per agent): W_head times the
+// mean over the first T tokens of RMSNorm(h) * g_final.  xm: d floats of LDS; 256 threads.  A token's scale is one wave's
+// work (one workgroup-wide sum per token after another took 22 us at T = 10, d = 512, now 14).
+__device__ __forceinline__ void mean_head_wg(const float* __restrict__ h, int S, int T, int d, float eps,
+                                             const float* __restrict__ gfin, const void* __restrict__ w, int wdtype, int n_out,
+                                             float* __restrict__ wp, float* xm) {
+  constexpr int TB = 16;
+  __shared__ float rs[TB];
+  const int b = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const float* hb = h + (int64_t)b * S * d;
+  for (int t0 = 0; t0 < T; t0 += TB) {
+    for (int t = t0 + wave; t < min(t0 + TB, T); t += 4) {
+      const float* hr = hb + (int64_t)t * d;
+      float ss = 0.f;
+#pragma unroll 8
+      for (int n = lane; n < d; n += WAVE) ss += hr[n] * hr[n];
+      ss = wave_sum(ss);
+      if (lane == 0) rs[t - t0] = 1.0f / sqrtf(ss / (float)d + eps);
+    }
+    __syncthreads();
+    for (int n = threadIdx.x; n < d; n += blockDim.x) {
+      const float gn = gfin[n];
+      float acc = t0 ? xm[n] : 0.f;
+#pragma unroll 5
+      for (int t = t0; t < min(t0 + TB, T); ++t) acc += hb[(int64_t)t * d + n] * rs[t - t0] * gn;
+      xm[n] = acc;
+    }
+    __syncthreads();
+  }
+  for (int o = wave; o < n_out; o += 4) {
+    float acc = 0.f;
+#pragma unroll 8
+    for (int n = lane; n < d; n += WAVE) acc += xm[n] * qh_weight(w, wdtype, (int64_t)o * d + n);
+    acc = wave_sum(acc);
+    if (lane == 0) wp[(int64_t)b * n_out + o] = acc / (float)T;
+  }
+}
+
 // Hidden units [64 g0, 64 g1) (groups of 64; units past `hidden` count nothing) of one agent's head, summed into the
 // 2 nq outputs without b2: emit(q, c, v) is called by lane 0 of a wave for every query q and coordinate c.
 // row(t, col): residual of expert token t (0 <= t < T), column col.  lds: nq * (d + 256) floats.  `ready()` runs after

@@ -217,7 +217,7 @@ struct GenericWeights {
   const float* attn_norm; const float* ffn_norm;
 };
 struct GenericWorkspace {
-  float* h; float* x; float* q; float* k; float* v; float* attn; float* g; float* u; float* rope;
+  float* h; float* q; float* k; float* v; float* attn; float* g; float* rope;
 };
 hipError_t generic_tick(const GenericWeights* layers, const float* final_norm, const void* head_w,
                         const QueryHead& qhead, int wdtype,
