@@ -494,10 +494,55 @@ size_t static_tick_layout(const fsx_expert* ex, const TickParams& tp, char* base
 }
 }  // namespace
 
-// Split plan of the per-phase attention over the cached rows: chunks of chunk_rows rows (a multiple of 32) so that the
-// work items (chunk, head, query tile) number about 2048, eight waves per CU, and fit the workspace.
-static void plan_chunks(const fsx_expert* ex, TickParams& tp, int64_t rows) {
+// Split plan of the per-phase attention.
+static void plan_chunks(const fsx_expert* ex, TickParams& tp, int64_t rows, bool shared) {
   const int H = ex->cfg.n_heads;
+  // Query tiles that share their rows (k_attention_tiles): an agent's, or those of the agents of a shared cache whose rings
+  // start at the same slot.
+  bool one_start = shared;
+  for (int b = 0, last = -1; b < tp.B && one_start; ++b)
+    if (tp.len[b] > 0) {
+      one_start = last < 0 || tp.start[b] == tp.start[last];
+      last = b;
+      tp.att_start = tp.start[b];
+    }
+  tp.att_shared = one_start && tp.B > 1;
+  if (tp.n_tt > 1 || tp.att_shared) {
+    const int q_all = tp.att_shared ? tp.B * tp.n_tt : tp.n_tt, gpa = (q_all + ATT_Q - 1) / ATT_Q;
+    tp.att_qg = (q_all + gpa - 1) / gpa;
+    tp.att_groups = ((q_all + tp.att_qg - 1) / tp.att_qg) * (tp.att_shared ? 1 : tp.B);
+    const int own = tp.att_shared ? 0 : (tp.S + 31) / 32;
+    int t_max = 1;
+    for (int b = 0; b < tp.B; ++b) t_max = std::max(t_max, (tp.len[b] + 31) / 32 + own);
+    // Chunks of `per` tiles: a workgroup fills a CU, so a plan costs its rounds of workgroups, each as long as its chunk and
+    // a start-up worth about four tiles; the cheapest of 1, 2, .. 32 chunks for the longest agent.
+    int best = t_max;
+    int64_t best_cost = INT64_MAX;
+    for (int k = 1; k <= 32 && k <= t_max; ++k) {
+      const int per = (t_max + k - 1) / k;
+      int64_t wgs = 0, chunks = 0;
+      for (int b = 0; b < tp.B; ++b) {
+        const int n = std::max(1, ((tp.len[b] + 31) / 32 + own + per - 1) / per);
+        chunks += n;
+        wgs += (int64_t)n * (tp.att_groups / tp.B);
+      }
+      if (tp.att_shared) wgs = (int64_t)k * tp.att_groups;
+      if (k > 1 && chunks * H * tp.n_tt > ex->items_max) break;
+      const int64_t cost = ((wgs * H + ex->cu_count - 1) / ex->cu_count) * (per + 4);
+      if (cost < best_cost) {
+        best_cost = cost;
+        best = per;
+      }
+    }
+    tp.chunk_rows = 32 * best;
+    tp.att_chunks = (t_max + best - 1) / best;
+    tp.chunk_prefix[0] = 0;
+    for (int b = 0; b < tp.B; ++b)
+      tp.chunk_prefix[b + 1] = tp.chunk_prefix[b] + std::max(1, ((tp.len[b] + 31) / 32 + own + best - 1) / best);
+    return;
+  }
+  // One wave per work item: chunks of chunk_rows cached rows (a multiple of 32) so that the items (chunk, head, query
+  // tile) number about 2048, eight waves per CU, and fit the workspace.
   const int64_t work = rows * H * tp.n_tt, target = 2048;
   int64_t cr = std::max<int64_t>(32, ((work + target - 1) / target + 31) / 32 * 32);
   for (;; cr *= 2) {
@@ -627,7 +672,7 @@ static int forward_impl(fsx_expert* ex, const fsx_cache_desc* cache, const void*
     g_err.clear();
     return FSX_OK;
   }
-  plan_chunks(ex, tp, rows);
+  plan_chunks(ex, tp, rows, cv.bs == 0);
   const int ks_o = gemm_split(tp.M, dm.d, dm.A), ks_d = gemm_split(tp.M, dm.d, dm.F);
 
   HIP_TRY(launch_embed(tokens, c.dtype, ex->fw[0].attn_norm, tp, dm, ex->ws, s));
@@ -883,7 +928,7 @@ extern "C" int fsx_backbone_append(fsx_backbone* bb, fsx_cache_desc* cache, cons
     cv.hs = cache->capacity * cache->head_dim;
     cv.rs = cache->head_dim;
   }
-  plan_chunks(ex, tp, rows);
+  plan_chunks(ex, tp, rows, false);
   const int ks_o = gemm_split(tp.M, dm.d, dm.A), ks_d = gemm_split(tp.M, dm.d, dm.F);
   HIP_TRY(launch_embed(tokens, c.dtype, ex->fw[0].attn_norm, tp, dm, ex->ws, s));
   for (int l = 0; l < c.n_layers; ++l) {

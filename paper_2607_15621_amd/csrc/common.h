@@ -220,6 +220,16 @@ __device__ __forceinline__ uint4 ld_global(const uint4* p) {
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 
+// Device-scope 16-byte accesses of `bytes` bytes at a wave-uniform base (buffer instructions take the cache policy as an
+// operand; a 64-bit atomic is the widest that the language has).  Not atomic beyond 32 bits: for data ordered by a flag or
+// a count.
+struct DevBuf {
+  __amdgpu_buffer_rsrc_t r;
+  __device__ __forceinline__ DevBuf(void* base, int bytes) : r(__builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, 0x00027000)) {}
+  __device__ __forceinline__ void store16(int off, u32x4_t v) const { __builtin_amdgcn_raw_buffer_store_b128(v, r, off, 0, 16); }
+  __device__ __forceinline__ u32x4_t load16(int off) const { return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 16); }
+};
+
 // Direct load global -> LDS of 16 bytes per lane: lane l's 16 bytes at src land at lds_base + 16 l
 // (lds_base is wave-uniform).  No registers hold the data; completion is counted by vmcnt.
 // COH: device-scope (sc1) load, for data produced inside the same launch.

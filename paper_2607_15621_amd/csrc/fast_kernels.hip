@@ -588,66 +588,160 @@ struct AttnArgs {
   int causal;          // the own rows are masked causally (new token t sees own rows 0..t)
 };
 
-// Log-sum-exp merge of the nslot states at items it0, it0 + step, ... (in that order) by one wave: lane l takes query
-// t0 + l / 16, channels 8 (l % 16) .. + 7; the states are loaded RB at a time, every load before any use.
-__device__ __forceinline__ void merge_items(const AttnArgs& a, int64_t it0, int64_t step, int nslot, int rows, int lane,
-                                            uint16_t* dst /* query 0, channel 0 */) {
+// A state in memory: 16-byte piece k of lane l (accumulator k, queries 4 (l / 16) .. + 3, channel 8 (l % 16) + k) at
+// float4 64 k + l of att_o + 2048 item, so every access is a run of whole lines (rows of queries that do not exist are
+// left out); the maximum and the sum of query c at att_ml + 32 item + c and + 16 + c.
+// Stored query by query in 8-byte words, the states of 74 queries over 4,096 rows (10 MB) took 12 to 18 us to store and
+// merge, now 6.
+__device__ __forceinline__ void store_state(const AttnArgs& a, int64_t item, const AttnState& st, float lt, int rows, int lane) {
+  const int grp = lane >> 4, c = lane & 15;
+  if (grp == 0 && c < rows) {
+    st_dev_f(a.att_ml + item * 32 + c, st.m);
+    st_dev_f(a.att_ml + item * 32 + 16 + c, lt);
+  }
+  if (4 * grp < rows) {
+    const DevBuf o(a.att_o + item * 2048, 8192);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) o.store16((64 * k + lane) * 16, __builtin_bit_cast(u32x4_t, st.o[k]));
+  }
+}
+
+// One query tile's output (its first `rows` rows at dst) from a whole state; lt: the sum of query c.
+__device__ __forceinline__ void write_output(const AttnArgs& a, const AttnState& st, float lt, int rows, int lane, uint16_t* dst) {
+  const int grp = lane >> 4, c = lane & 15;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float inv = 1.0f / col_pick(lt, grp, i);
+    if (4 * grp + i < rows)
+      *reinterpret_cast<uint4*>(dst + (int64_t)(4 * grp + i) * a.A + 8 * c) =
+          make_uint4(pack_bf16x2(st.o[0][i] * inv, st.o[1][i] * inv), pack_bf16x2(st.o[2][i] * inv, st.o[3][i] * inv),
+                     pack_bf16x2(st.o[4][i] * inv, st.o[5][i] * inv), pack_bf16x2(st.o[6][i] * inv, st.o[7][i] * inv));
+  }
+}
+
+// Log-sum-exp merge of the nslot states at items it0, it0 + step, ... (in that order) for queries 4 qq .. + 3 by one wave:
+// lane l takes channels 8 (l % 16) + 2 (l / 16) and the next of every query, and for the weights, 16 slots at a time, query
+// l % 4 of slot l / 4.  Few workgroups run this, each from a cold instruction cache, so it is kept short: with the weights
+// computed by every lane and 7 to 8 slots unrolled it took 8 to 9 us for 3 rounds of 8 slots, now 5.
+__device__ __forceinline__ void merge_queries(const AttnArgs& a, int64_t it0, int64_t step, int nslot, int qq, int rows, int lane,
+                                              uint16_t* dst /* query 0, channel 0 */) {
   constexpr int RB = 8;
-  const int d0 = 8 * (lane & 15);
-  for (int t0 = 0; t0 < rows; t0 += 4) {
-    const int t = min(t0 + (lane >> 4), rows - 1);
-    float M = -INFINITY, L = 0.f, acc[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) acc[k] = 0.f;
-    for (int s0 = 0; s0 < nslot; s0 += RB) {
-      float m[RB], l[RB];
-      float4 x0[RB], x1[RB];
+  const int kk = 2 * (lane >> 4), c = lane & 15;
+  auto over_slots = [](float v, auto op) {  // over the lanes of one query
+    v = op(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x124, 0xF, 0xF, false)));
+    return op(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x128, 0xF, 0xF, false)));
+  };
+  float M = -INFINITY, L = 0.f;
+  f32x4 o0 = {0.f, 0.f, 0.f, 0.f}, o1 = o0;
+  auto lane_value = [](float v, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); };
+  for (int s0 = 0; s0 < nslot; s0 += 16) {
+    const int sl = s0 + (lane >> 2);
+    const float* ml = a.att_ml + (it0 + step * min(sl, nslot - 1)) * 32 + 4 * qq + (lane & 3);
+    float m = ld_dev_f(ml), l = ld_dev_f(ml + 16);
+    const int ns = min(16, nslot - s0);
+    for (int j0 = 0; j0 < ns; j0 += RB) {
+      f32x4 x0[RB], x1[RB];
 #pragma unroll
       for (int j = 0; j < RB; ++j) {
-        const int64_t item = it0 + step * min(s0 + j, nslot - 1);
-        m[j] = ld_dev_f(a.att_ml + item * 32 + 2 * t);
-        l[j] = ld_dev_f(a.att_ml + item * 32 + 2 * t + 1);
-        const float* po = a.att_o + (item * 16 + t) * a.Dh + d0;
-        x0[j] = ld_dev_f4(po);
-        x1[j] = ld_dev_f4(po + 4);
+        const DevBuf o(a.att_o + (it0 + step * (s0 + min(j0 + j, ns - 1))) * 2048, 8192);
+        x0[j] = __builtin_bit_cast(f32x4, o.load16((64 * kk + 16 * qq + c) * 16));
+        x1[j] = __builtin_bit_cast(f32x4, o.load16((64 * kk + 64 + 16 * qq + c) * 16));
       }
+      if (j0 == 0) {  // the weights of these 16 slots, in m
+        if (sl >= nslot) m = -INFINITY;
+        const float mn = fmaxf(M, rows_max(over_slots(m, vmax))), mz = mn == -INFINITY ? 0.f : mn;
+        m = __builtin_amdgcn_exp2f(m - mz);
+        const float fa = __builtin_amdgcn_exp2f(M - mz);
+        L = L * fa + rows_sum(over_slots(sl < nslot ? l * m : 0.f, [](float x, float y) { return x + y; }));
+        M = mn;
 #pragma unroll
-      for (int j = 0; j < RB; ++j) {
-        if (s0 + j < nslot) {
-          const float mn = fmaxf(M, m[j]);
-          const float fa = M == -INFINITY ? 0.f : exp2f(M - mn), fb = exp2f(m[j] - mn);
-          L = L * fa + l[j] * fb;
-          acc[0] = acc[0] * fa + x0[j].x * fb; acc[1] = acc[1] * fa + x0[j].y * fb;
-          acc[2] = acc[2] * fa + x0[j].z * fb; acc[3] = acc[3] * fa + x0[j].w * fb;
-          acc[4] = acc[4] * fa + x1[j].x * fb; acc[5] = acc[5] * fa + x1[j].y * fb;
-          acc[6] = acc[6] * fa + x1[j].z * fb; acc[7] = acc[7] * fa + x1[j].w * fb;
-          M = mn;
+        for (int i = 0; i < 4; ++i) {
+          const float f = lane_value(fa, i);
+          o0[i] *= f;
+          o1[i] *= f;
         }
       }
-    }
-    if (t0 + (lane >> 4) < rows) {
-      const float inv = 1.0f / L;
-      *reinterpret_cast<uint4*>(dst + (int64_t)t * a.A + d0) =
-          make_uint4(pack_bf16x2(acc[0] * inv, acc[1] * inv), pack_bf16x2(acc[2] * inv, acc[3] * inv),
-                     pack_bf16x2(acc[4] * inv, acc[5] * inv), pack_bf16x2(acc[6] * inv, acc[7] * inv));
+#pragma unroll
+      for (int j = 0; j < RB; ++j)
+        if (j0 + j < ns)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float f = lane_value(m, 4 * (j0 + j) + i);
+            o0[i] += x0[j][i] * f;
+            o1[i] += x1[j][i] * f;
+          }
     }
   }
+  const float inv = 1.0f / L;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if (4 * qq + i < rows) {
+      const float f = lane_value(inv, i);
+      *reinterpret_cast<uint32_t*>(dst + (int64_t)(4 * qq + i) * a.A + 8 * c + kk) = pack_bf16x2(o0[i] * f, o1[i] * f);
+    }
+}
+
+// The wave's number, known to be the same in its lanes (what depends on it stays in scalar registers).
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
+
+// The per-agent arrays of the kernel arguments, one agent per lane: one round trip for all of them, where scalar loads by
+// agent wait for one another (arguments are cold in every launch).
+struct AgentLanes {
+  int len, prefix, prefix1;
+  int64_t start;
+  __device__ __forceinline__ AgentLanes(const TickParams& tp, int lane) {
+    static_assert(FSX_MAX_BATCH == WAVE, "an agent per lane");
+    len = tp.len[lane];
+    prefix = tp.chunk_prefix[lane];
+    prefix1 = tp.chunk_prefix[lane + 1];
+    start = tp.start[lane];
+  }
+  static __device__ __forceinline__ int pick(int v, int b) { return __builtin_amdgcn_readlane(v, b); }
+  __device__ __forceinline__ int64_t start_of(int b) const {
+    return (int64_t)((uint64_t)(uint32_t)pick((int)(start >> 32), b) << 32 | (uint32_t)pick((int)start, b));
+  }
+};
+
+// The end of a work item (one wave's state of 16 queries): the output itself if the agent has one chunk, else the state to
+// its slot, and the merge by the wave that finishes last.  first, nslot: the agent's chunks; cs: this one (first <= cs).
+__device__ __forceinline__ void finish_item(const AttnArgs& a, const TickParams& tp, const AttnState& st, int b, int h, int tt,
+                                            int first, int nslot, int cs, int lane) {
+  const int rows = min(16, tp.S - tt * 16);
+  const int64_t item = ((int64_t)cs * a.H + h) * tp.n_tt + tt;
+  const float lt = rows_sum(st.l);
+  uint16_t* out = a.attn_out + ((int64_t)b * tp.S + tt * 16) * a.A + (int64_t)h * a.Dh;
+  if (nslot == 1) {
+    write_output(a, st, lt, rows, lane, out);
+    return;
+  }
+  store_state(a, item, st, lt, rows, lane);
+  stores_done();
+  uint32_t* cnt = a.acnt + ((int64_t)b * a.H + h) * tp.n_tt + tt;
+  uint32_t done = 0;
+  if (lane == 0) done = __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  done = (uint32_t)__builtin_amdgcn_readfirstlane((int)done);
+  if (done != (uint32_t)(nslot - 1)) return;
+  if (lane == 0) __hip_atomic_store(cnt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  asm volatile("" ::: "memory");
+  const int64_t step = (int64_t)a.H * tp.n_tt;  // items between two chunks of the agent
+  for (int qq = 0; 4 * qq < rows; ++qq)
+    merge_queries(a, (int64_t)first * step + (int64_t)h * tp.n_tt + tt, step, nslot, qq, rows, lane, out);
 }
 
 template <int KT>
 __global__ __launch_bounds__(256) void k_attention(AttnArgs a, TickParams tp) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wave = wave_id(), lane = threadIdx.x & 63;
   const int item = blockIdx.x * (blockDim.x >> 6) + wave;
   if (item >= tp.n_items) return;
   const int tt = item % tp.n_tt;
   const int rest = item / tp.n_tt;
   const int h = rest % a.H;
   const int cs = rest / a.H;
-  int b = 0;
-  while (b + 1 < tp.B && tp.chunk_prefix[b + 1] <= cs) ++b;
-  const int first = tp.chunk_prefix[b], nslot = tp.chunk_prefix[b + 1] - first, cidx = cs - first;
+  const AgentLanes al(tp, lane);
+  const int b = __popcll(__ballot(lane < tp.B && al.prefix1 <= cs));
+  const int first = al.pick(al.prefix, b), nslot = al.pick(al.prefix1, b) - first, cidx = cs - first, len = al.pick(al.len, b);
   const int grp = lane >> 4, c = lane & 15;
-  const int t = tt * 16 + c, rows = min(16, tp.S - tt * 16);
+  const int t = tt * 16 + c;
   const bool tv = t < tp.S;
   const int64_t qrow = ((int64_t)b * tp.S + (tv ? t : 0)) * a.A + (int64_t)h * a.Dh;
   uint4 qf[4];
@@ -656,7 +750,7 @@ __global__ __launch_bounds__(256) void k_attention(AttnArgs a, TickParams tp) {
   for (int k = 0; k < 8; ++k) st.o[k] = f32x4{0.f, 0.f, 0.f, 0.f};
   st.m = -INFINITY;
   st.l = 0.f;
-  const int i0 = cidx * tp.chunk_rows, i1 = min(i0 + tp.chunk_rows, tp.len[b]);
+  const int i0 = cidx * tp.chunk_rows, i1 = min(i0 + tp.chunk_rows, len);
   if (i0 < i1) {
     constexpr int ES = KT == 0 ? 2 : 1;
     // ring slot 0 of (agent, layer, head); slots are a.cv.rs elements apart
@@ -671,7 +765,7 @@ __global__ __launch_bounds__(256) void k_attention(AttnArgs a, TickParams tp) {
     // chunks start at rows equal modulo the chunk, rings are often a power of two: every item would stream addresses
     // equal modulo that, so each starts at a tile of its own
     const int n = (i1 - i0 + 31) / 32;
-    attn_rows<KT, true>((const char*)a.cv.k + off, (const char*)a.cv.v + off, a.cv.rs * ES, tp.start[b], a.cv.cap, i0, i1,
+    attn_rows<KT, true>((const char*)a.cv.k + off, (const char*)a.cv.v + off, a.cv.rs * ES, al.start_of(b), a.cv.cap, i0, i1,
                         (int)((5u * h + 3u * b + cidx) % (unsigned)n), qf, ks, lane, st);
     if (KT == 1)
 #pragma unroll
@@ -683,40 +777,276 @@ __global__ __launch_bounds__(256) void k_attention(AttnArgs a, TickParams tp) {
     attn_rows<0, false>((const char*)a.kself + off, (const char*)a.vself + off, (int64_t)a.A * 2, 0, 0, 0, tp.S, 0, qf, 1.f,
                         lane, st, a.causal ? tt * 16 : 1 << 30);
   }
-  const float lt = rows_sum(st.l);
-  uint16_t* out = a.attn_out + ((int64_t)b * tp.S + tt * 16) * a.A + (int64_t)h * a.Dh;
-  if (nslot == 1) {
+  finish_item(a, tp, st, b, h, tt, first, nslot, cs, lane);
+}
+
+// The same for agents whose query tiles share their rows: several query tiles per agent, or several agents on one shared
+// cache.  Workgroup = (head, group of up to ATT_Q query tiles, chunk of tp.chunk_rows rows): two loader waves bring the
+// chunk's 32-row tiles of K and V into LDS by direct loads of whole rows, two tiles per step, three steps deep (as in
+// k_gemm_rows: the loaders take the steps in turn), and each compute wave takes one query tile.  The own rows follow the
+// cached ones in the list of tiles; on a shared cache, where they differ from agent to agent, each wave takes them by
+// itself.  The last workgroup of a (head, group) merges its chunks, four queries per wave at a time.
+// One wave per query tile reading its rows by itself fetched every tile once per query tile and had nothing in flight while
+// it computed.  Per layer: 74 queries over 4,096 rows 111 -> 28 us (2 to the arguments, 4 to the first step, 13 for 17
+// tiles -- 64 KiB in flight per CU, bound by memory -- and 6 to store and merge), fp8 100 -> 31; the 40 blocks of a clip
+// over one cache 40 -> 14.  Six compute waves and two loaders: two waves per SIMD leave each 256 registers; with eight and
+// four, 168 each, the tiles' operands spilled.
+//
+// Places of a lane's operands in a tile: k[kb] of row c (and 16 rows on) for channels 32 kb + 8 grp .., v[j] of row 4 grp + j
+// (and 16 rows on) for channels 8 c ..  Kept in registers; computed at each use they were hoisted, once per use, and spilled.
+template <int KT>
+struct LdsPlaces {
+  static constexpr int RB = KT == 0 ? 256 : 128;  // bytes of a row
+  int k[4], v[4];
+  static __device__ __forceinline__ int place(int row, int e) {
+    return KT == 0 ? row * 256 + (((e >> 3) ^ (row & 15)) << 4) : row * 128 + (((e >> 4) ^ ((row >> 1) & 7)) << 4) + (e & 8);
+  }
+  __device__ __forceinline__ explicit LdsPlaces(int lane) {
+    const int c = lane & 15, grp = lane >> 4;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      k[j] = place(c, 32 * j + 8 * grp);
+      v[j] = place(4 * grp + j, 8 * c);
+    }
+  }
+};
+
+constexpr int AT_TILE = 16384;  // LDS of a tile: K rows, then V rows
+
+// Rows [0, nv) of the NT 32-row tiles in LDS into the state; query c sees rows up to qmax + c.  The state's maximum moves
+// only when a score exceeds it by more than 2^8 (or is the first), so probabilities stay below 2^8.
+template <int KT, int NT>
+__device__ __forceinline__ void attn_lds_tiles(const char* tile, int nv, int qmax, const uint4 (&qf)[4], float kscale, int lane,
+                                               const LdsPlaces<KT>& at, AttnState& st) {
+  constexpr int R16 = 16 * LdsPlaces<KT>::RB;
+  const int c = lane & 15, grp = lane >> 4;
+  f32x4 s[2 * NT];
+#pragma unroll
+  for (int r = 0; r < 2 * NT; ++r) {
+    uint4 kf[4];
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) kf[kb] = load8<KT>(tile + at.k[kb] + (r / 2 * AT_TILE + (r & 1) * R16));
+    s[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) s[r] = KT == 0 ? mfma_bf16(kf[kb], qf[kb], s[r]) : mfma_f16(kf[kb], qf[kb], s[r]);
+    if (KT == 1) s[r] *= kscale;
+    if (r & 1) __builtin_amdgcn_sched_barrier(0);  // or the compiler has every operand in registers at once, and spills
+  }
+  const bool edge = nv < 32 * NT;
+  if (edge || qmax < 32 * NT) {  // rows past the agent's, or of later new tokens: no weight
+#pragma unroll
+    for (int r = 0; r < 2 * NT; ++r)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int rr = 16 * r + 4 * grp + i;
+        if (rr >= nv || rr > qmax + c) s[r][i] = -INFINITY;
+      }
+  }
+  float mx = vmax(s[0][0], s[0][1]);
+#pragma unroll
+  for (int r = 0; r < 2 * NT; ++r) mx = vmax3(r ? vmax3(mx, s[r][0], s[r][1]) : mx, s[r][2], s[r][3]);
+  mx = rows_max(mx);
+  if (__any(mx > st.m + 8.0f)) {
+    const float m_new = fmaxf(st.m, mx);
+    const float alpha = __builtin_amdgcn_exp2f(st.m - (m_new == -INFINITY ? 0.f : m_new));
+    st.l *= alpha;
+    st.m = m_new;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float inv = 1.0f / col_pick(lt, grp, i);
-      if (4 * grp + i < rows)
-        *reinterpret_cast<uint4*>(out + (int64_t)(4 * grp + i) * a.A + 8 * c) =
-            make_uint4(pack_bf16x2(st.o[0][i] * inv, st.o[1][i] * inv), pack_bf16x2(st.o[2][i] * inv, st.o[3][i] * inv),
-                       pack_bf16x2(st.o[4][i] * inv, st.o[5][i] * inv), pack_bf16x2(st.o[6][i] * inv, st.o[7][i] * inv));
-    }
-    return;
-  }
-  if (grp == 0 && c < rows) {
-    st_dev_f(a.att_ml + (int64_t)item * 32 + 2 * c, st.m);
-    st_dev_f(a.att_ml + (int64_t)item * 32 + 2 * c + 1, lt);
-  }
+      const float a_i = col_pick(alpha, grp, i);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    if (4 * grp + i < rows) {
-      float* dst = a.att_o + ((int64_t)item * 16 + 4 * grp + i) * a.Dh + 8 * c;
-      st_dev_f4(dst, make_float4(st.o[0][i], st.o[1][i], st.o[2][i], st.o[3][i]));
-      st_dev_f4(dst + 4, make_float4(st.o[4][i], st.o[5][i], st.o[6][i], st.o[7][i]));
+      for (int k = 0; k < 8; ++k) st.o[k][i] *= a_i;
     }
   }
+  const float mz = st.m == -INFINITY ? 0.f : st.m;  // no row seen yet
+  float ps = 0.f;
+#pragma unroll
+  for (int r = 0; r < 2 * NT; ++r)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      s[r][i] = __builtin_amdgcn_exp2f(s[r][i] - mz);
+      ps += s[r][i];
+    }
+  st.l += ps;
+#pragma unroll
+  for (int u = 0; u < NT; ++u) {
+    uint4 vr[8], vt[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) vr[j] = load8<KT>(tile + at.v[j & 3] + (u * AT_TILE + 8192 + (j >> 2) * R16));
+    if (edge)  // the values of rows past the agent's are not the agent's
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (32 * u + (j < 4 ? 4 * grp + j : 12 + 4 * grp + j) >= nv) vr[j] = make_uint4(0, 0, 0, 0);
+    const f32x4 p0 = s[2 * u], p1 = s[2 * u + 1];
+    uint4 pf;
+    if (KT == 0)
+      pf = make_uint4(pack_bf16x2(p0[0], p0[1]), pack_bf16x2(p0[2], p0[3]), pack_bf16x2(p1[0], p1[1]), pack_bf16x2(p1[2], p1[3]));
+    else
+      pf = make_uint4(pack_f16x2(p0[0], p0[1]), pack_f16x2(p0[2], p0[3]), pack_f16x2(p1[0], p1[1]), pack_f16x2(p1[2], p1[3]));
+    transpose8x8_b16(vr, vt);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) st.o[k] = KT == 0 ? mfma_bf16(pf, vt[k], st.o[k]) : mfma_f16(pf, vt[k], st.o[k]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+template <int KT>
+__global__ __launch_bounds__((ATT_Q + 2) * 64) void k_attention_tiles(AttnArgs a, TickParams tp) {
+  extern __shared__ __align__(16) char at_lds[];  // three buffers of two tiles
+  __shared__ uint32_t last;
+  const int wave = wave_id(), lane = threadIdx.x & 63, grp = lane >> 4, c = lane & 15;
+  const AgentLanes al(tp, lane);
+  const int h = blockIdx.x % a.H, rest = blockIdx.x / a.H, n_groups = tp.att_groups, g = rest % n_groups, cidx = rest / n_groups;
+  const bool shared = tp.att_shared;
+  const int qg = tp.att_qg, gpa = shared ? 1 : n_groups / tp.B;  // query tiles of a group, groups of an agent
+  const int q0 = shared ? g * qg : (g % gpa) * qg, q1 = min(q0 + qg, shared ? tp.B * tp.n_tt : tp.n_tt);
+  auto agent_of = [&](int q) { return shared ? q / tp.n_tt : g / gpa; };
+  const int b_first = agent_of(q0), per = tp.chunk_rows / 32, own_tiles = shared ? 0 : (tp.S + 31) / 32;
+  int len_max = 0;  // of the group's agents
+  for (int b = b_first; b <= agent_of(q1 - 1); ++b) len_max = max(len_max, al.pick(al.len, b));
+  const int nt = (len_max + 31) / 32 + own_tiles;
+  const int t0 = cidx * per, n = min(per, nt - t0);  // this chunk's tiles t0 .. t0 + n - 1
+  if (n <= 0 && cidx > 0) return;
+  const int ns = (n + 1) / 2, n_chunks = max(1, (nt + per - 1) / per);
+  if (wave >= qg) {
+    constexpr int ES = KT == 0 ? 2 : 1;
+    const int par = wave - qg;
+    const int64_t cap = a.cv.cap, start = shared ? tp.att_start : al.start_of(b_first);
+    const int64_t off = cache_head_base(a.cv, b_first, a.cv.layer, h) * ES;
+    const int ct = nt - own_tiles;
+    // step i, 16-byte chunk k of row r at position k ^ (r & 15) (fp8: k ^ ((r >> 1) & 7)), so that the rows of an operand
+    // read fall in distinct banks
+    auto stage = [&](int i) {
+      for (int u = 0; u < 2 && 2 * i + u < n; ++u) {
+        const int t = t0 + 2 * i + u;
+        char* dst = at_lds + (i % 3 * 2 + u) * AT_TILE;
+        if (t < ct) {
+          constexpr int RPI = KT == 0 ? 4 : 8, CPR = 64 / RPI;  // rows of a load, 16-byte chunks of a row
+#pragma unroll
+          for (int q = 0; q < 32 / RPI; ++q) {
+            const int r = q * RPI + lane / CPR, ch = (lane % CPR) ^ (KT == 0 ? r & 15 : (r >> 1) & 7);
+            int64_t slot = start + min(32 * t + r, len_max - 1);
+            if (slot >= cap) slot -= cap;
+            const int64_t src = off + slot * a.cv.rs * ES + ch * 16;
+            load_lds16<false>((const char*)a.cv.k + src, dst + q * 1024);
+            load_lds16<false>((const char*)a.cv.v + src, dst + 8192 + q * 1024);
+          }
+        } else {
+          const int64_t base = (int64_t)b_first * tp.S * a.A + (int64_t)h * a.Dh;
+#pragma unroll
+          for (int q = 0; q < 8; ++q) {
+            const int r = q * 4 + grp, ch = c ^ (r & 15);
+            const int64_t src = base + (int64_t)min(32 * (t - ct) + r, tp.S - 1) * a.A + ch * 8;
+            load_lds16<false>(a.kself + src, dst + q * 1024);
+            load_lds16<false>(a.vself + src, dst + 8192 + q * 1024);
+          }
+        }
+      }
+    };
+    if (par < ns) stage(par);
+    if (par == 0) vm_wait_all();
+    wg_barrier();
+    for (int i = 0; i + 1 < ns; ++i) {  // while step i is computed
+      if ((i & 1) == par) {
+        if (i + 2 < ns) stage(i + 2);
+      } else {
+        vm_wait_all();  // step i + 1
+      }
+      wg_barrier();
+    }
+  } else {
+    const bool active = q0 + wave < q1;
+    const int q = min(q0 + wave, q1 - 1), b = agent_of(q), tt = shared ? q % tp.n_tt : q;  // this wave's query tile
+    const int len = al.pick(al.len, b), ct = (len + 31) / 32;
+    const int first = al.pick(al.prefix, b), nslot = al.pick(al.prefix1, b) - first;
+    const int t = tt * 16 + c;
+    const bool tv = t < tp.S;
+    const int64_t qrow = ((int64_t)b * tp.S + (tv ? t : 0)) * a.A + (int64_t)h * a.Dh;
+    AttnState st;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) st.o[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+    st.m = -INFINITY;
+    st.l = 0.f;
+    float ks = 1.f, vs = 1.f;
+    if (KT == 1 && len > 0) {
+      const int64_t si = cache_scale_index(a.cv, b, a.cv.layer, h);
+      ks = a.cv.k_scale[si];
+      vs = a.cv.v_scale[si];
+    }
+    uint4 qf[4];
+    load_q_frag<KT>(a.q, qrow, tv, grp, qf);
+    const LdsPlaces<KT> at(lane);
+    const LdsPlaces<0> at_own(lane);
+    bool codes = KT == 1;  // the state still counts cached rows in codes, the queries are in fp16
+    auto to_own = [&]() {
+      if (KT == 1 && codes) {
+        codes = false;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) st.o[k] *= vs;
+        load_q_frag<0>(a.q, qrow, tv, grp, qf);
+      }
+    };
+    wg_barrier();
+    for (int i = 0; i < ns; ++i) {
+      const int ti = t0 + 2 * i, nu = min(2, n - 2 * i);
+      const char* tile = at_lds + i % 3 * 2 * AT_TILE;
+      if (active) {
+        // both tiles of the step at once where they are of one kind
+        const int nc = max(0, min(nu, ct - ti));  // cached ones
+        if (nc == 2)
+          attn_lds_tiles<KT, 2>(tile, min(64, len - 32 * ti), 64, qf, ks, lane, at, st);
+        else if (nc == 1)
+          attn_lds_tiles<KT, 1>(tile, min(32, len - 32 * ti), 32, qf, ks, lane, at, st);
+        if (!shared && nc < nu) {
+          to_own();
+          const int r0 = 32 * (ti + nc - ct), qmax = a.causal ? tt * 16 - r0 : 64;
+          if (qmax + 15 >= 0) {
+            if (nu - nc == 2)
+              attn_lds_tiles<0, 2>(tile, min(64, tp.S - r0), qmax, qf, 1.f, lane, at_own, st);
+            else
+              attn_lds_tiles<0, 1>(tile + nc * AT_TILE, min(32, tp.S - r0), qmax, qf, 1.f, lane, at_own, st);
+          }
+        }
+      }
+      if (i + 1 < ns) wg_barrier();
+    }
+    if (shared && active && cidx == nslot - 1) {  // the own rows of this wave's agent
+      to_own();
+      const int64_t off = ((int64_t)b * tp.S * a.A + (int64_t)h * a.Dh) * 2;
+      attn_rows<0, false>((const char*)a.kself + off, (const char*)a.vself + off, (int64_t)a.A * 2, 0, 0, 0, tp.S, 0, qf, 1.f,
+                          lane, st, a.causal ? tt * 16 : 1 << 30);
+    }
+    if (KT == 1 && codes)
+#pragma unroll
+      for (int k = 0; k < 8; ++k) st.o[k] *= vs;
+    if (active && cidx < nslot) {
+      const int rows = min(16, tp.S - tt * 16);
+      const float lt = rows_sum(st.l);
+      if (nslot == 1)
+        write_output(a, st, lt, rows, lane, a.attn_out + ((int64_t)b * tp.S + tt * 16) * a.A + (int64_t)h * a.Dh);
+      else
+        store_state(a, ((int64_t)(first + cidx) * a.H + h) * tp.n_tt + tt, st, lt, rows, lane);
+    }
+  }
+  if (n_chunks == 1) return;
+  // the last workgroup of the (head, group) merges
   stores_done();
-  uint32_t* cnt = a.acnt + ((int64_t)b * a.H + h) * tp.n_tt + tt;
-  uint32_t done = 0;
-  if (lane == 0) done = __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  done = (uint32_t)__builtin_amdgcn_readfirstlane((int)done);
-  if (done != (uint32_t)(nslot - 1)) return;
-  if (lane == 0) __hip_atomic_store(cnt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  const int64_t step = (int64_t)a.H * tp.n_tt;  // items between two chunks of the agent
-  merge_items(a, (int64_t)first * step + (int64_t)h * tp.n_tt + tt, step, nslot, rows, lane, out);
+  wg_barrier();
+  if (threadIdx.x == 0) {
+    uint32_t* cnt = a.acnt + (int64_t)g * a.H + h;
+    last = __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(n_chunks - 1);
+    if (last) __hip_atomic_store(cnt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  if (!last) return;
+  const int64_t step = (int64_t)a.H * tp.n_tt;
+  for (int i = wave; i < 4 * (q1 - q0); i += qg + 2) {
+    const int q = q0 + (i >> 2), qq = i & 3, b = agent_of(q), tt = shared ? q % tp.n_tt : q, rows = min(16, tp.S - tt * 16);
+    const int first = al.pick(al.prefix, b), nslot = al.pick(al.prefix1, b) - first;
+    if (nslot > 1 && 4 * qq < rows)
+      merge_queries(a, (int64_t)first * step + (int64_t)h * tp.n_tt + tt, step, nslot, qq, rows, lane,
+                    a.attn_out + ((int64_t)b * tp.S + tt * 16) * a.A + (int64_t)h * a.Dh);
+  }
 }
 
 hipError_t launch_attention(const CacheView& cv, const TickParams& tp, const Dims& dm, const Workspace& ws,
@@ -724,6 +1054,15 @@ hipError_t launch_attention(const CacheView& cv, const TickParams& tp, const Dim
   AttnArgs a{};
   a.cv = cv; a.q = ws.q; a.kself = ws.kself; a.vself = ws.vself; a.att_o = ws.att_o; a.att_ml = ws.att_ml;
   a.acnt = ws.acnt; a.attn_out = ws.attn; a.H = dm.H; a.Dh = dm.Dh; a.A = dm.A; a.causal = causal ? 1 : 0;
+  if (tp.att_groups) {
+    const auto fn = cv.dtype == FSX_FP8_E4M3 ? k_attention_tiles<1> : k_attention_tiles<0>;
+    constexpr int lds = 3 * 2 * 16384;
+    // above the default limit of 64 KiB; per device and set on each launch (a cheap host call)
+    const hipError_t e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(fn, dim3((unsigned)(dm.H * tp.att_groups * tp.att_chunks)), dim3(64 * (tp.att_qg + 2)), lds, s, a, tp);
+    return hipGetLastError();
+  }
   const int wpg = tp.n_items >= 1024 ? 4 : 1;
   const dim3 grid((unsigned)((tp.n_items + wpg - 1) / wpg)), block(64 * wpg);
   if (cv.dtype == FSX_FP8_E4M3)
@@ -749,11 +1088,30 @@ __device__ __forceinline__ void write_row_chunk(const RowsInto& w, int64_t i);
 // x = bf16(h / rms(h)) for the next projection (whose packed weights carry the norm gain).  One workgroup
 // per token row.
 // =====================================================================================================
+constexpr int RN_T = 128;
+// The sum of ksplit partials of four columns, every load issued before any add (in order of the partials).
+__device__ __forceinline__ float4 sum_partials(const float* __restrict__ part, int64_t idx, int64_t stride, int ksplit) {
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int s0 = 0; s0 < ksplit; s0 += 8) {
+    float4 v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      v[j] = s0 + j < ksplit ? *reinterpret_cast<const float4*>(part + (s0 + j) * stride + idx) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      acc.x += v[j].x;
+      acc.y += v[j].y;
+      acc.z += v[j].z;
+      acc.w += v[j].w;
+    }
+  }
+  return acc;
+}
+
 template <bool ROWS>
-__global__ __launch_bounds__(256) void k_reduce_norm(float* __restrict__ h, const float* __restrict__ part,
-                                                     uint16_t* __restrict__ xb, int M, int d, int ksplit,
-                                                     const float* __restrict__ gain, float eps,
-                                                     float* __restrict__ hidden, RowsInto w) {
+__global__ __launch_bounds__(RN_T) void k_reduce_norm(float* __restrict__ h, const float* __restrict__ part,
+                                                      uint16_t* __restrict__ xb, int M, int d, int ksplit, float eps,
+                                                      float* __restrict__ hidden, RowsInto w) {
   __shared__ float red[16];
   const int m = blockIdx.x;
   if (ROWS && m >= M) {
@@ -761,20 +1119,28 @@ __global__ __launch_bounds__(256) void k_reduce_norm(float* __restrict__ h, cons
     return;
   }
   float ss = 0.f;
-  for (int n = threadIdx.x; n < d; n += blockDim.x) {
+  float4 val = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int n = 4 * threadIdx.x; n < d; n += 4 * RN_T) {
     const int64_t idx = (int64_t)m * d + n;
-    float acc = 0.f;
-    for (int s = 0; s < ksplit; ++s) acc += part[((int64_t)s * M + m) * d + n];
-    const float v = h[idx] + acc;
-    h[idx] = v;
-    if (hidden) hidden[idx] = v;
-    ss += v * v;
+    const float4 h0 = *reinterpret_cast<const float4*>(h + idx);
+    const float4 acc = sum_partials(part, idx, (int64_t)M * d, ksplit);
+    val = make_float4(h0.x + acc.x, h0.y + acc.y, h0.z + acc.z, h0.w + acc.w);
+    *reinterpret_cast<float4*>(h + idx) = val;
+    if (hidden) {  // the caller's buffer: 4-byte alignment only
+      hidden[idx] = val.x;
+      hidden[idx + 1] = val.y;
+      hidden[idx + 2] = val.z;
+      hidden[idx + 3] = val.w;
+    }
+    ss += val.x * val.x + val.y * val.y + val.z * val.z + val.w * val.w;
   }
   ss = block_sum(ss, red);
   const float r = 1.0f / sqrtf(ss / (float)d + eps);
-  for (int n = threadIdx.x; n < d; n += blockDim.x) {
+  for (int n = 4 * threadIdx.x; n < d; n += 4 * RN_T) {
     const int64_t idx = (int64_t)m * d + n;
-    xb[idx] = f32_to_bf16(h[idx] * r);  // the gain is folded into the packed weights
+    if (d > 4 * RN_T) val = *reinterpret_cast<const float4*>(h + idx);
+    // the gain is folded into the packed weights
+    *reinterpret_cast<uint2*>(xb + idx) = make_uint2(pack_bf16x2(val.x * r, val.y * r), pack_bf16x2(val.z * r, val.w * r));
   }
 }
 
@@ -797,21 +1163,7 @@ __global__ __launch_bounds__(RN_CHUNK / 4) void k_reduce_chunks(float* __restric
   }
   // thread t: the 4 columns ch * RN_CHUNK + 4t .. + 3, 16-byte loads (every partial's load issued before any add)
   const int64_t idx = (int64_t)m * d + ch * RN_CHUNK + 4 * threadIdx.x;
-  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int s0 = 0; s0 < ksplit; s0 += 8) {
-    float4 v[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-      v[j] = s0 + j < ksplit ? *reinterpret_cast<const float4*>(part + (int64_t)(s0 + j) * M * d + idx)
-                             : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      acc.x += v[j].x;
-      acc.y += v[j].y;
-      acc.z += v[j].z;
-      acc.w += v[j].w;
-    }
-  }
+  const float4 acc = sum_partials(part, idx, (int64_t)M * d, ksplit);
   const float4 h0 = *reinterpret_cast<const float4*>(h + idx);
   const float4 val = make_float4(h0.x + acc.x, h0.y + acc.y, h0.z + acc.z, h0.w + acc.w);
   *reinterpret_cast<float4*>(h + idx) = val;
@@ -849,7 +1201,7 @@ hipError_t launch_reduce_norm(const TickParams& tp, const Dims& dm, const Worksp
     for (int b = 0; b < tp.B; ++b) w.first[b] = (tp.start[b] + tp.len[b]) % rows_into->cap;
     chunks = (int64_t)tp.B * tp.S * rows_into->H * (rows_into->Dh / 8);
   }
-  const int nt = wide_rows(dm) ? RN_CHUNK / 4 : 256, own = wide_rows(dm) ? tp.M * (dm.d / RN_CHUNK) : tp.M;
+  const int nt = wide_rows(dm) ? RN_CHUNK / 4 : RN_T, own = wide_rows(dm) ? tp.M * (dm.d / RN_CHUNK) : tp.M;
   const dim3 grid((unsigned)(own + (chunks + nt - 1) / nt)), block(nt);
   if (wide_rows(dm)) {
     const auto fn = rows_into ? k_reduce_chunks<true> : k_reduce_chunks<false>;
@@ -857,7 +1209,7 @@ hipError_t launch_reduce_norm(const TickParams& tp, const Dims& dm, const Worksp
                        ws.rs, ws.rcnt, dm.eps, w);
   } else {
     const auto fn = rows_into ? k_reduce_norm<true> : k_reduce_norm<false>;
-    hipLaunchKernelGGL(fn, grid, block, 0, s, ws.h, (const float*)ws.part, ws.xb, tp.M, dm.d, ksplit, gain, dm.eps,
+    hipLaunchKernelGGL(fn, grid, block, 0, s, ws.h, (const float*)ws.part, ws.xb, tp.M, dm.d, ksplit, dm.eps,
                        hidden_layer, w);
   }
   return hipGetLastError();

@@ -15,6 +15,10 @@ struct TickParams {
   int32_t n_tt;                               // ceil(S / 16): query tiles per (agent, head)
   int32_t chunk_rows;                         // per-phase path: cache rows per attention work item
   int32_t n_items;                            // per-phase path: attention work items
+  // per-phase path, query tiles that share rows (k_attention_tiles): groups of att_qg query tiles (0 groups: one wave per
+  // item instead), the longest group's chunks, whether a group spans the agents of a shared cache, and their ring start
+  int32_t att_groups, att_qg, att_chunks, att_shared;
+  int64_t att_start;
   int32_t Mp;                                 // M rounded up to 8: rows of tile-major activations
   int32_t Ms;                                 // M rounded up to 32: rows of the sums of squares
   int64_t pos[FSX_MAX_BATCH];                 // rotary position of token 0
@@ -110,6 +114,7 @@ hipError_t launch_embed(const void* tokens, int tok_dtype, const float* g0, cons
 // projection applies the RMSNorm row scales from the chunk sums of squares.
 hipError_t launch_gemm_qkv(const FastWeights& w, const TickParams& tp, const Dims& dm, const Workspace& ws,
                            hipStream_t s, bool after_reduction);
+constexpr int ATT_Q = 6;  // query tiles of a workgroup that share their rows at most
 // The attention of every (agent, head), its work items (tp.chunk_prefix, tp.n_items) merged.
 hipError_t launch_attention(const CacheView& cv, const TickParams& tp, const Dims& dm, const Workspace& ws,
                             hipStream_t s, bool causal = false);

@@ -1,0 +1,85 @@
+"""The per-phase attention over query tiles that share rows, at the sizes where its plan can go wrong, against the fp64
+oracle: two to seven query tiles (one group and two), cached rows at and past the 32 of a tile and the two tiles of a
+step, empty agents, one chunk and several, rings that wrap, both layouts, bf16 and fp8; a shared cache whose agents start
+at one slot (their query tiles share workgroups) and at different ones (they do not).  Keys are of the kind that moves a
+query's running maximum (outlier channels, a growing scale, a sink row), so that a wrong row shows.  Tolerances as in the
+parity tests: 2e-2 of the largest value, the bf16 rounding of 2 layers' operands."""
+
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+import synth
+from harness import Cache, Model, record, rel_err, run_forward, tokens_for
+from paper_2607_15621_amd import fsx
+
+pytestmark = pytest.mark.gpu
+
+TOL = 2e-2
+
+
+def workload(name, wid, lengths, frame, cache="bf16", heads=8, capacity=None, stress=True):
+    return synth.Workload(name=name, wid=wid, n_layers=2, d_model=256, n_heads=heads, head_dim=128, d_ffn=512,
+                          n_expert_tokens=10, n_frame_tokens=frame, batch=len(lengths), lengths=tuple(lengths),
+                          dtype="bf16", cache_dtype=cache, capacity=capacity or max(max(lengths), 1) + 3,
+                          stress_keys=stress)
+
+
+# frame tokens, lengths, cache dtype, token-major
+CASES = [(7, (0, 1, 33), "bf16", False), (23, (31, 32, 64, 65), "fp8", True), (87, (700, 0, 95), "bf16", True),
+         (95, (2100,), "bf16", False), (64, (1500, 40), "fp8", False), (6, (5000,), "fp8", True)]
+
+
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_query_tiles_sharing_rows_match_oracle(case):
+    frame, lengths, cache_dtype, token_major = CASES[case]
+    print(f"case phase attention {CASES[case]}", flush=True)
+    wl = workload(f"phatt{case}", 760 + case, lengths, frame, cache_dtype, heads=2 if max(lengths) > 1000 else 8)
+    model = Model(wl)
+    ex = model.create(flags=fsx.FLAG_MULTI_LAUNCH)
+    cache = Cache(wl, starts=[(wl.capacity - 5 + 3 * b) % wl.capacity for b in range(wl.batch)],
+                  layout=fsx.CACHE_TOKEN_MAJOR if token_major else fsx.CACHE_HEAD_MAJOR)
+    host_tok, tok = tokens_for(wl)
+    wp, hid = run_forward(ex, cache, tok, wl.batch, frame, with_hidden=True)
+    for b in range(wl.batch):
+        ref_wp, ref_hid = model.oracle_agent(host_tok[b], cache.oracle_rows(b, decoded=True), cache.desc.pos[b])
+        record(b, rel_err(wp[b], ref_wp), TOL)
+        record(b, max(rel_err(hid[l, b], ref_hid[l]) for l in range(wl.n_layers)), TOL, what="worst layer hidden")
+    wp2, hid2 = run_forward(ex, cache, tok, wl.batch, frame, with_hidden=True)
+    assert np.array_equal(wp, wp2) and np.array_equal(hid, hid2), "two forwards differ bitwise"
+    ex.close()
+
+
+@pytest.mark.parametrize("flags", [0, fsx.FLAG_MULTI_LAUNCH])
+@pytest.mark.parametrize("starts_differ,frame,rows", [(False, 0, 170), (False, 20, 64), (True, 0, 170), (False, 0, 3000)])
+def test_agents_of_a_shared_cache_match_oracle(flags, starts_differ, frame, rows):
+    """Agent j sees the first lens[j] rows from its start: some none, some a part of the longest agent's last tile."""
+    print(f"case shared attention {flags} {starts_differ} {frame} {rows}", flush=True)
+    lens = [rows, 0, rows // 2 + 1, 32, rows - 1, 33, 1]
+    starts = [5 * j if starts_differ else 9 for j in range(len(lens))]
+    wl = workload("phshared", 780, lens, frame, capacity=rows + 40, heads=8)
+    model = Model(wl)
+    ex = model.create(flags=flags)
+    full = Cache(wl.replace(batch=1, lengths=(rows + 40,)))  # every slot of the ring holds a row
+    desc = fsx.CacheDesc(full.k, full.v, fsx.BF16, wl.n_layers, wl.n_heads, wl.head_dim, wl.capacity, lens, positions=lens,
+                         starts=starts, layout=fsx.CACHE_SHARED)
+    host_tok, tok = tokens_for(wl)
+    n = len(lens)
+    wp = torch.full((n, wl.n_out), float("nan"), device="cuda")
+    fsx.expert_forward(ex, desc, tok, n, frame, wp, None)
+    torch.cuda.synchronize()
+    slab = full.oracle_rows(0)
+    for j in range(n):
+        slots = (starts[j] + np.arange(lens[j])) % wl.capacity
+        ref, _ = model.oracle_agent(host_tok[j], lambda l: tuple(x[slots] for x in slab(l)), lens[j])
+        record(j, rel_err(wp[j].cpu().numpy(), ref), TOL)
+    if rows == 170 and not starts_differ:  # what only the longest agent sees does not reach the others
+        full.k[:, :, :, (9 + rows - 1) % wl.capacity] = float("nan")
+        full.v[:, :, :, (9 + rows - 1) % wl.capacity] = float("nan")
+        wp2 = torch.zeros_like(wp)
+        fsx.expert_forward(ex, desc, tok, n, frame, wp2, None)
+        torch.cuda.synchronize()
+        assert torch.isnan(wp2[0]).all() and torch.equal(wp2[1:], wp[1:])
+    ex.close()
