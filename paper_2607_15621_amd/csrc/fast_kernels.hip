@@ -296,6 +296,8 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
   }
 }
 
+constexpr int SHORT_CHUNKS = 4;  // chunks of a K range that LDS holds whole
+
 // Workgroup barrier without the fence that drains global loads: the callers order LDS themselves.
 __device__ __forceinline__ void wg_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -313,7 +315,12 @@ __device__ __forceinline__ void wg_barrier() {
 // rows themselves, in register batches of two k-blocks: 64 rows 48, 63, 44 -> 28, 38, 35; 512 rows 298, 400, 271 -> 62,
 // 115, 80.  Bound: the lines a CU can have in flight (see cu_cost), at 512 rows with the MFMAs busy a third of the time;
 // one loader wave was the bound before (12 GB/s per CU), and operands read two at a time cost 40 % of the 512-row q/k/v.
-template <int MT, int NT, int KCB, int RING, int EPI, int CW>
+//
+// ALL: a K range of at most four chunks (512 columns of bf16, the expert's width), which LDS holds whole: every load is
+// issued at once.  With three buffers the last chunks waited for the first to be multiplied, and the round trips were most
+// of the expert's projections.  us for q/k/v, gate/up, O + down: 74 rows 10.9, 8.6, 13.8, now 9.9, 7.2, 10.8; 160 rows 15.2,
+// 9.8, 15.1, now 10.2, 7.6, 12.4 (with row blocks of 80 instead of 128).
+template <int MT, int NT, int KCB, int RING, int EPI, int CW, bool ALL>
 __global__ __launch_bounds__((CW + 4) * 64) void k_gemm_rows(GemmArgs g, int n_rb) {
   constexpr int CPR = KCB * 4;         // 16-byte chunks of a row in one LDS chunk
   constexpr int RPI = 64 / CPR;        // rows one direct-load instruction brings
@@ -321,7 +328,8 @@ __global__ __launch_bounds__((CW + 4) * 64) void k_gemm_rows(GemmArgs g, int n_r
   static_assert(CPR >= 8 && CPR <= 64 && NI % 2 == 0, "chunk size");
   static_assert(RING % KCB == 0 || KCB % RING == 0, "chunk and ring sizes");
   constexpr int UN = RING > KCB ? RING : KCB;  // k-blocks per unrolled pass
-  __shared__ uint4 xs[3][MT * 16 * CPR];
+  constexpr int NB = ALL ? SHORT_CHUNKS : 3;
+  __shared__ uint4 xs[NB][MT * 16 * CPR];
   __shared__ float rs[MT * 16];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int c = lane & 15, grp = lane >> 4;
@@ -345,7 +353,7 @@ __global__ __launch_bounds__((CW + 4) * 64) void k_gemm_rows(GemmArgs g, int n_r
     // (the 16 rows of an operand read then fall in distinct banks); rows past M and k-blocks past the range repeat the
     // last one
     auto stage = [&](int i) {
-      uint4* buf = xs[i % 3];
+      uint4* buf = xs[i % NB];
 #pragma unroll 8
       for (int qq = 0; qq < NI / 2; ++qq) {
         const int q = 2 * qq + half;
@@ -355,13 +363,20 @@ __global__ __launch_bounds__((CW + 4) * 64) void k_gemm_rows(GemmArgs g, int n_r
       }
     };
     if (par < nch) stage(par);
-    if (par == 0) vm_wait_all();
+    if (ALL && par + 2 < nch) stage(par + 2);
+    auto arrived = [&](int i) {  // chunk i, which this wave staged
+      if (ALL && i + 2 < nch)
+        vm_wait_below_c<NI / 2>();
+      else
+        vm_wait_all();
+    };
+    if (par == 0) arrived(0);
     wg_barrier();
     for (int i = 0; i + 1 < nch; ++i) {  // while chunk i is multiplied
       if ((i & 1) == par) {
-        if (i + 2 < nch) stage(i + 2);
+        if (!ALL && i + 2 < nch) stage(i + 2);
       } else {
-        vm_wait_all();  // chunk i + 1
+        arrived(i + 1);
       }
       wg_barrier();
     }
@@ -401,7 +416,7 @@ __global__ __launch_bounds__((CW + 4) * 64) void k_gemm_rows(GemmArgs g, int n_r
         if (!CHECK || kb + j + 1 < kb1) {
           if (j % KCB == KCB - 1) {
             wg_barrier();
-            buf = buf == 2 ? 0 : buf + 1;
+            buf = buf == NB - 1 ? 0 : buf + 1;
           }
           read((j + 1) % KCB, xv[(j + 1) & 1]);
           __builtin_amdgcn_sched_barrier(0);
@@ -441,11 +456,11 @@ __global__ __launch_bounds__((CW + 4) * 64) void k_gemm_rows(GemmArgs g, int n_r
   }
 }
 
-template <int MT, int NT, int KCB, int RING, int EPI, int CW = 4>
+template <int MT, int NT, int KCB, int RING, int EPI, int CW = 4, bool ALL = false>
 static hipError_t launch_rows(const GemmArgs& g, hipStream_t s) {
   const int n_rb = (g.M + MT * 16 - 1) / (MT * 16), n_cg = (g.N / 16 + CW * NT - 1) / (CW * NT);
   const int combos = n_cg * g.ksplit;
-  hipLaunchKernelGGL((k_gemm_rows<MT, NT, KCB, RING, EPI, CW>), dim3((unsigned)((combos + 7) / 8 * 8 * n_rb)), dim3((CW + 4) * 64), 0, s,
+  hipLaunchKernelGGL((k_gemm_rows<MT, NT, KCB, RING, EPI, CW, ALL>), dim3((unsigned)((combos + 7) / 8 * 8 * n_rb)), dim3((CW + 4) * 64), 0, s,
                      g, n_rb);
   return hipGetLastError();
 }
@@ -489,6 +504,41 @@ int gemm_split(int M, int N, int K) {
   return best;
 }
 
+// More than 64 rows over a K range that LDS holds whole: row tiles (5 or 8) and column tiles of a workgroup, by its rounds of
+// 256 workgroups, each a start-up (about 6 us, the time of 1,270 lines at the 27 GB/s of a CU) and its lines of both.
+template <int EPI>
+static hipError_t gemm_short(const GemmArgs& g, hipStream_t s) {
+  const int n_mt = (g.M + 15) / 16, tiles = g.N / 16, kbs = (g.K / 32 + g.ksplit - 1) / g.ksplit;
+  static constexpr int opt_mt[] = {5, 8}, opt_t[] = {1, 2, 3, 4, 6, 8, 12};
+  int mt = 5, tpw = 1;
+  int64_t best = INT64_MAX;
+  for (int m : opt_mt)
+    for (int t : opt_t) {
+      const int64_t wgs = (int64_t)((tiles + t - 1) / t) * g.ksplit * ((n_mt + m - 1) / m);
+      const int64_t cost = (wgs + 255) / 256 * (1270 + 8 * (t + m) * kbs);
+      if (cost < best) {
+        best = cost;
+        mt = m;
+        tpw = t;
+      }
+    }
+#define FSX_SHORT(M)                                                 \
+  switch (tpw) {                                                     \
+    case 1: return launch_rows<M, 1, 4, 16, EPI, 1, true>(g, s);     \
+    case 2: return launch_rows<M, 1, 4, 16, EPI, 2, true>(g, s);     \
+    case 3: return launch_rows<M, 1, 4, 16, EPI, 3, true>(g, s);     \
+    case 4: return launch_rows<M, 1, 4, 16, EPI, 4, true>(g, s);     \
+    case 6: return launch_rows<M, 1, 4, 8, EPI, 6, true>(g, s);      \
+    case 8: return launch_rows<M, 2, 4, 8, EPI, 4, true>(g, s);      \
+    default: return launch_rows<M, 3, 4, 4, EPI, 4, true>(g, s);     \
+  }
+  if (mt == 5) {
+    FSX_SHORT(5)
+  }
+  FSX_SHORT(8)
+#undef FSX_SHORT
+}
+
 template <int EPI>
 static hipError_t gemm_dispatch(const GemmArgs& g, hipStream_t s) {
   const int n_mt = (g.M + 15) / 16, tiles = g.N / 16;
@@ -517,6 +567,7 @@ static hipError_t gemm_dispatch(const GemmArgs& g, hipStream_t s) {
       default: return launch_rows<4, 2, 4, 8, EPI, 4>(g, s);
     }
   }
+  if (g.K / 32 <= SHORT_CHUNKS * 4 * g.ksplit) return gemm_short<EPI>(g, s);
   switch (tpw) {
     case 3: return launch_rows<8, 1, 4, 8, EPI, 3>(g, s);
     case 4: return launch_rows<8, 1, 4, 8, EPI, 4>(g, s);
@@ -788,8 +839,8 @@ __global__ __launch_bounds__(256) void k_attention(AttnArgs a, TickParams tp) {
 // itself.  The last workgroup of a (head, group) merges its chunks, four queries per wave at a time.
 // One wave per query tile reading its rows by itself fetched every tile once per query tile and had nothing in flight while
 // it computed.  Per layer: 74 queries over 4,096 rows 111 -> 28 us (2 to the arguments, 4 to the first step, 13 for 17
-// tiles -- 64 KiB in flight per CU, bound by memory -- and 6 to store and merge), fp8 100 -> 31; the 40 blocks of a clip
-// over one cache 40 -> 14.  Six compute waves and two loaders: two waves per SIMD leave each 256 registers; with eight and
+// tiles -- 64 KiB in flight per CU, bound by memory -- and 6 to store and merge); the 40 blocks of a clip over one cache
+// 40 -> 14; 74 queries over 16,000 fp8 rows 6,960 -> 3,670 per tick.  Six compute waves and two loaders: two waves per SIMD leave each 256 registers; with eight and
 // four, 168 each, the tiles' operands spilled.
 //
 // Places of a lane's operands in a tile: k[kb] of row c (and 16 rows on) for channels 32 kb + 8 grp .., v[j] of row 4 grp + j
@@ -892,7 +943,7 @@ __device__ __forceinline__ void attn_lds_tiles(const char* tile, int nv, int qma
 
 template <int KT>
 __global__ __launch_bounds__((ATT_Q + 2) * 64) void k_attention_tiles(AttnArgs a, TickParams tp) {
-  extern __shared__ __align__(16) char at_lds[];  // three buffers of two tiles
+  __shared__ __align__(16) char at_lds[3 * 2 * AT_TILE];  // three buffers of two tiles
   __shared__ uint32_t last;
   const int wave = wave_id(), lane = threadIdx.x & 63, grp = lane >> 4, c = lane & 15;
   const AgentLanes al(tp, lane);
@@ -1056,11 +1107,7 @@ hipError_t launch_attention(const CacheView& cv, const TickParams& tp, const Dim
   a.acnt = ws.acnt; a.attn_out = ws.attn; a.H = dm.H; a.Dh = dm.Dh; a.A = dm.A; a.causal = causal ? 1 : 0;
   if (tp.att_groups) {
     const auto fn = cv.dtype == FSX_FP8_E4M3 ? k_attention_tiles<1> : k_attention_tiles<0>;
-    constexpr int lds = 3 * 2 * 16384;
-    // above the default limit of 64 KiB; per device and set on each launch (a cheap host call)
-    const hipError_t e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(fn, dim3((unsigned)(dm.H * tp.att_groups * tp.att_chunks)), dim3(64 * (tp.att_qg + 2)), lds, s, a, tp);
+    hipLaunchKernelGGL(fn, dim3((unsigned)(dm.H * tp.att_groups * tp.att_chunks)), dim3(64 * (tp.att_qg + 2)), 0, s, a, tp);
     return hipGetLastError();
   }
   const int wpg = tp.n_items >= 1024 ? 4 : 1;
