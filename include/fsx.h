@@ -71,7 +71,8 @@ enum {
 enum {
   FSX_FLAG_GENERIC = 1,     /* force the simple per-op kernels instead of the fused tick kernel */
   FSX_FLAG_MULTI_LAUNCH = 2, /* run the fused path as one launch per phase instead of one persistent launch */
-  FSX_FLAG_TRACE = 4         /* tick kernel records per-workgroup phase timestamps (fsx_expert_trace) */
+  FSX_FLAG_TRACE = 4         /* every tick is one persistent launch and records per-workgroup phase timestamps
+                                (fsx_expert_trace) */
 };
 
 #define FSX_MAX_BATCH 64
@@ -185,7 +186,7 @@ int fsx_expert_forward(fsx_expert* ex, const fsx_cache_desc* cache, const void* 
 
 /* The same tick as fsx_expert_forward, for callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): it allocates nothing, neither in the call nor
- * through the handle's workspace.  The tick kernel's workspace lives in a static device array of the library of
+ * through the handle's workspace.  The workspace lives in a static device array of the library of
  * 48 MiB per device (held until the process ends; its device address is looked up on the first call on a device).
  * Each call first clears the part of that array that must start at zero, with a kernel on `stream`, so a call does
  * not depend on what an earlier call left there; calls that overlap on one device (other streams or threads) race
@@ -313,7 +314,7 @@ const char* fsx_last_error(void);
 
 /* Introspection of a handle (any pointer may be NULL):
  *   path          0 = fused bf16 path (one persistent launch per tick, or one launch per phase with
- *                 FSX_FLAG_MULTI_LAUNCH), 1 = simple per-op kernels
+ *                 FSX_FLAG_MULTI_LAUNCH and where a tick's rows are many), 1 = simple per-op kernels
  *   weight_bytes  bytes of the packed weight matrices the tick streams (excludes fp32 norm gains)
  *   workspace_bytes device workspace owned by the handle */
 int fsx_expert_info(const fsx_expert* ex, int32_t* path, int64_t* weight_bytes, int64_t* workspace_bytes);

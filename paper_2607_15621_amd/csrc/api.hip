@@ -492,6 +492,31 @@ size_t static_tick_layout(const fsx_expert* ex, const TickParams& tp, char* base
   }
   return off;
 }
+
+// The same for the workspace of one launch per phase.  States of attention items are needed only where an agent has several
+// chunks.
+size_t static_phase_layout(const fsx_expert* ex, const TickParams& tp, char* base, Workspace& w, size_t* zero_off) {
+  const fsx_expert_cfg& c = ex->cfg;
+  const size_t d = c.d_model, F = c.d_ffn, Dh = c.head_dim, A = ex->A, M = tp.M, H = c.n_heads;
+  const size_t items = tp.chunk_prefix[tp.B] > tp.B ? (size_t)tp.chunk_prefix[tp.B] * H * tp.n_tt : 0;
+  const std::pair<void**, size_t> parts[] = {
+      {(void**)&w.h, M * d * 4}, {(void**)&w.xb, M * d * 2}, {(void**)&w.q, M * A * 4}, {(void**)&w.kself, M * A * 2},
+      {(void**)&w.vself, M * A * 2}, {(void**)&w.attn, M * A * 2}, {(void**)&w.z, M * F * 2},
+      {(void**)&w.part, KSPLIT_MAX * M * d * 4}, {(void**)&w.att_o, items * 16 * Dh * 4}, {(void**)&w.att_ml, items * 32 * 4},
+      {(void**)&w.rope, M * Dh * 4}, {(void**)&w.ss, M * (d / 512 + 1) * 4}, {(void**)&w.rs, M * 4},
+      {nullptr, 0},  // start of the part that must start at zero
+      {(void**)&w.rcnt, M * 4}, {(void**)&w.acnt, (size_t)tp.B * H * tp.n_tt * 4}};
+  size_t off = 0;
+  for (const auto& p : parts) {
+    if (!p.first) {
+      *zero_off = off;
+      continue;
+    }
+    if (base) *p.first = base + off;
+    off += (p.second + 255) & ~(size_t)255;
+  }
+  return off;
+}
 }  // namespace
 
 // Split plan of the per-phase attention.
@@ -558,6 +583,21 @@ static void plan_chunks(const fsx_expert* ex, TickParams& tp, int64_t rows, bool
   tp.chunk_rows = (int)cr;
 }
 
+// Whether a tick that the persistent kernel could run is faster as one launch per phase.  The kernel takes its rows in blocks
+// of 80, each as one more round of every phase, and streams the cache of an agent of many queries through one loader wave per
+// CU; a launch per phase costs about 3 us whatever the rows.  us per tick of the full expert, kernel and phases:
+//   several query tiles per agent, 224 to 4,000 cached rows: 60 rows of tokens 1,579 to 1,678 and 1,597 to 1,692, 74 rows
+//     1,677 to 2,185 and 1,590 to 1,983, 148 rows 2,251 and 1,736, 400 rows 5,676 and 3,694;
+//   agents of one shared cache: 80 rows 1,326 and 1,546, 120 rows 2,019 and 1,636, 400 rows 5,202 and 2,279;
+//   one query tile per agent, over few cached rows: 80 rows 1,526 and 1,707, 100 rows 1,885 and 1,795, 160 rows 2,265 and
+//     1,923; the kernel streams long histories better (120 rows over 24,000 in all 3,803 and 4,283) up to two full blocks
+//     (160 rows over 16,384 in all 3,347 and 3,123, over 32,000 4,688 and 4,460).
+static bool phases_faster(const TickParams& tp, int64_t rows) {
+  if (tp.n_tt > 1) return tp.M > 64;
+  if (tp.att_shared) return tp.M > 96;
+  return tp.M > 144 || (tp.M > 96 && rows <= 8192);
+}
+
 static int forward_impl(fsx_expert* ex, const fsx_cache_desc* cache, const void* tokens, int32_t batch,
                         int32_t n_frame_tokens, float* waypoints, float* hidden, void* stream, bool use_static) {
   if (!ex) return fail(FSX_E_INVALID, "expert handle is NULL");
@@ -618,13 +658,34 @@ static int forward_impl(fsx_expert* ex, const fsx_cache_desc* cache, const void*
     return FSX_OK;
   }
 
+  plan_chunks(ex, tp, rows, cv.bs == 0);
+  Workspace ws = ex->ws;
+  size_t zoff = 0;
+  bool phases = !ex->tick;
   if (ex->tick) {
+    const int G = ex->cu_count;
+    tp.Mp = (tp.M + 7) / 8 * 8;
+    tp.Ms = (tp.M + 31) / 32 * 32;
+    // partial-state slots per XCD: at most one per segment (<= 4 local heads per agent) plus one per slice boundary
+    // (the kernel checks the bound and fails the tick if the placement breaks it)
+    tp.slot_x = batch * 4 + (use_static ? ex->wg_per_xcd_max : G);
+    if (phases_faster(tp, rows) && !(c.flags & FSX_FLAG_TRACE)) {
+      // Both entry points take the same path, so that their results are the same: phases, if the static array holds their
+      // workspace, or if it does not hold the kernel's either (the allocation-free entry point then refuses the call).
+      TickParams st = tp;
+      st.slot_x = batch * 4 + ex->wg_per_xcd_max;
+      TickArgs dummy = ex->ta;
+      size_t z = 0;
+      phases = static_phase_layout(ex, tp, nullptr, ws, &zoff) <= STATIC_SCRATCH_BYTES;
+      const size_t need = static_tick_layout(ex, st, nullptr, dummy, &z);
+      if (need > STATIC_SCRATCH_BYTES) phases = !use_static;
+    }
+  }
+  if (!phases) {
     int per_cu = 0;
     HIP_TRY(tick_occupancy(cache->dtype == FSX_FP8_E4M3 ? 1 : 0, &per_cu));
     if (per_cu < 1) return fail(FSX_E_UNSUPPORTED, "tick kernel does not fit on a compute unit");
     const int G = ex->cu_count;
-    tp.Mp = (tp.M + 7) / 8 * 8;
-    tp.Ms = (tp.M + 31) / 32 * 32;
     // row blocks per residual column tile: about one piece per workgroup, pieces of at least 16 rows (the pieces
     // number at most G <= XFLAGS, the flag slots of f_out and f_mid)
     tp.rblk = std::max(1, std::min(G / (dm.d / 16), (tp.M + 15) / 16));
@@ -640,13 +701,9 @@ static int forward_impl(fsx_expert* ex, const fsx_cache_desc* cache, const void*
       tp.seg_w[k] = (int)((tp.len[b] + 31) / 32) + (tp.S + 31) / 32;
       tp.seg_p[k + 1] = tp.seg_p[k] + tp.seg_w[k];
     }
-    // partial-state slots per XCD: at most one per segment (<= 4 local heads per agent) plus one per slice boundary
-    // (the kernel checks the bound and fails the tick if the placement breaks it)
-    tp.slot_x = batch * 4 + (use_static ? ex->wg_per_xcd_max : G);
     TickArgs a = ex->ta;
     if (use_static) {
       // the workspace for this call's sizes, laid over the static array; epoch 1 on flags cleared by this call
-      size_t zoff = 0;
       const size_t need = static_tick_layout(ex, tp, nullptr, a, &zoff);
       if (need > STATIC_SCRATCH_BYTES)
         return fail(FSX_E_CAPACITY, "this call needs " + std::to_string(need) + " bytes of workspace; the static array "
@@ -672,26 +729,32 @@ static int forward_impl(fsx_expert* ex, const fsx_cache_desc* cache, const void*
     g_err.clear();
     return FSX_OK;
   }
-  plan_chunks(ex, tp, rows, cv.bs == 0);
+  if (use_static) {
+    void* base = nullptr;
+    rc = scratch_of(dev, &base);
+    if (rc) return rc;
+    const size_t need = static_phase_layout(ex, tp, (char*)base, ws, &zoff);
+    HIP_TRY(launch_fill_zero((char*)base + zoff, need - zoff, s));
+  }
   const int ks_o = gemm_split(tp.M, dm.d, dm.A), ks_d = gemm_split(tp.M, dm.d, dm.F);
 
-  HIP_TRY(launch_embed(tokens, c.dtype, ex->fw[0].attn_norm, tp, dm, ex->ws, s));
+  HIP_TRY(launch_embed(tokens, c.dtype, ex->fw[0].attn_norm, tp, dm, ws, s));
   for (int l = 0; l < c.n_layers; ++l) {
     const FastWeights& w = ex->fw[l];
     cv.layer = l;
-    HIP_TRY(launch_gemm_qkv(w, tp, dm, ex->ws, s, l > 0));
-    HIP_TRY(launch_attention(cv, tp, dm, ex->ws, s));
-    HIP_TRY(launch_gemm_o(w, tp, dm, ex->ws, ks_o, s));
-    HIP_TRY(launch_reduce_norm(tp, dm, ex->ws, ks_o, w.ffn_norm, nullptr, s));
-    HIP_TRY(launch_gemm_gu(w, tp, dm, ex->ws, s));
-    HIP_TRY(launch_gemm_down(w, tp, dm, ex->ws, ks_d, s));
+    HIP_TRY(launch_gemm_qkv(w, tp, dm, ws, s, l > 0));
+    HIP_TRY(launch_attention(cv, tp, dm, ws, s));
+    HIP_TRY(launch_gemm_o(w, tp, dm, ws, ks_o, s));
+    HIP_TRY(launch_reduce_norm(tp, dm, ws, ks_o, w.ffn_norm, nullptr, s));
+    HIP_TRY(launch_gemm_gu(w, tp, dm, ws, s));
+    HIP_TRY(launch_gemm_down(w, tp, dm, ws, ks_d, s));
     const float* gnext = l + 1 < c.n_layers ? ex->fw[l + 1].attn_norm : ex->final_norm;
-    HIP_TRY(launch_reduce_norm(tp, dm, ex->ws, ks_d, gnext, hidden ? hidden + (int64_t)l * tp.M * dm.d : nullptr, s));
+    HIP_TRY(launch_reduce_norm(tp, dm, ws, ks_d, gnext, hidden ? hidden + (int64_t)l * tp.M * dm.d : nullptr, s));
   }
   if (c.head_kind == FSX_HEAD_QUERY_MLP)
-    HIP_TRY(launch_query_head(ex->ws.h, tp, dm, ex->final_norm, ex->qhead, waypoints, s));
+    HIP_TRY(launch_query_head(ws.h, tp, dm, ex->final_norm, ex->qhead, waypoints, s));
   else
-    HIP_TRY(launch_head(tp, dm, ex->ws, ex->final_norm, ex->head_w, c.dtype, waypoints, s));
+    HIP_TRY(launch_head(tp, dm, ws, ex->final_norm, ex->head_w, c.dtype, waypoints, s));
   HIP_TRY(hipEventRecord(ex->done, s));
   g_err.clear();
   return FSX_OK;

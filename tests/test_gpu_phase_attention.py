@@ -83,3 +83,37 @@ def test_agents_of_a_shared_cache_match_oracle(flags, starts_differ, frame, rows
         torch.cuda.synchronize()
         assert torch.isnan(wp2[0]).all() and torch.equal(wp2[1:], wp[1:])
     ex.close()
+
+
+# agents, frame tokens, cached rows of each, shared cache, whether a launch per phase is the faster form
+ROUTES = [(2, 22, 40, False, False), (3, 12, 40, False, True), (9, 0, 40, False, False), (10, 0, 40, False, True),
+          (10, 0, 820, False, False), (15, 0, 820, False, True), (9, 0, 40, True, False), (10, 0, 40, True, True)]
+
+
+@pytest.mark.parametrize("batch,frame,rows,shared,phases", ROUTES)
+def test_route_of_a_tick_by_its_rows(batch, frame, rows, shared, phases):
+    """The default handle takes the faster form on both sides of every line, and so does the allocation-free entry point."""
+    print(f"case route {batch} {frame} {rows} {shared}", flush=True)
+    wl = workload("phroute", 790, (rows,) * batch, frame, heads=2)
+    model = Model(wl)
+    cache = Cache(wl.replace(batch=1, lengths=(rows,)) if shared else wl)
+    if shared:
+        cache.desc = fsx.CacheDesc(cache.k, cache.v, fsx.BF16, wl.n_layers, wl.n_heads, wl.head_dim, wl.capacity,
+                                   [rows] * batch, positions=[rows] * batch, layout=fsx.CACHE_SHARED)
+    host_tok, tok = tokens_for(wl)
+    got = {}
+    for name, flags in (("default", 0), ("phases", fsx.FLAG_MULTI_LAUNCH), ("kernel", fsx.FLAG_TRACE)):
+        ex = model.create(flags=flags)
+        got[name] = run_forward(ex, cache, tok, batch, frame, with_hidden=True)
+        if name == "default":
+            wp = torch.full((batch, wl.n_out), float("nan"), device="cuda")
+            hid = torch.full((wl.n_layers, batch, wl.seq, wl.d_model), float("nan"), device="cuda")
+            fsx.expert_forward_noalloc(ex, cache.desc, tok, batch, frame, wp, hid)
+            torch.cuda.synchronize()
+            got["noalloc"] = wp.cpu().numpy(), hid.cpu().numpy()
+        ex.close()
+    same = lambda a, b: all(np.array_equal(x, y) for x, y in zip(got[a], got[b]))  # noqa: E731
+    assert not same("phases", "kernel"), "the two forms agree bitwise: the test could not tell them apart"
+    assert same("default", "phases" if phases else "kernel") and same("noalloc", "default")
+    for x, y in zip(got["phases"], got["kernel"]):
+        assert rel_err(x, y) <= TOL
