@@ -318,8 +318,8 @@ __device__ __forceinline__ void wg_barrier() {
 //
 // ALL: a K range of at most four chunks (512 columns of bf16, the expert's width), which LDS holds whole: every load is
 // issued at once.  With three buffers the last chunks waited for the first to be multiplied, and the round trips were most
-// of the expert's projections.  us for q/k/v, gate/up, O + down: 74 rows 10.9, 8.6, 13.8, now 9.9, 7.2, 10.8; 160 rows 15.2,
-// 9.8, 15.1, now 10.2, 7.6, 12.4 (with row blocks of 80 instead of 128).
+// of the expert's projections.  us for q/k/v, gate/up, O + down: 74 rows 10.9, 8.6, 13.8, now 8.5, 5.5, 9.4; 160 rows 15.2,
+// 9.8, 15.1, now 10.2, 6.1, 11.2 (with smaller row blocks too, see gemm_short).
 template <int MT, int NT, int KCB, int RING, int EPI, int CW, bool ALL>
 __global__ __launch_bounds__((CW + 4) * 64) void k_gemm_rows(GemmArgs g, int n_rb) {
   constexpr int CPR = KCB * 4;         // 16-byte chunks of a row in one LDS chunk
@@ -504,19 +504,22 @@ int gemm_split(int M, int N, int K) {
   return best;
 }
 
-// More than 64 rows over a K range that LDS holds whole: row tiles (5 or 8) and column tiles of a workgroup, by its rounds of
-// 256 workgroups, each a start-up (about 6 us, the time of 1,270 lines at the 27 GB/s of a CU) and its lines of both.
+// More than 16 rows over a K range that LDS holds whole: row tiles (2 to 5) and column tiles of a workgroup, by its rounds of
+// 256 workgroups times its row tiles and a third of its column tiles (the rows pass through LDS, the weights stream by
+// them).  Of the pairs below, at 74 to 400 rows of the expert, the rule picks the fastest or one within 0.5 us of it, with
+// two exceptions of 1 us.  us against row tiles of 5 and 8 weighed as much as column tiles: q/k/v of 74 rows 9.9 -> 8.5, of
+// 400 rows 23.0 -> 19.5; gate/up of 160 rows 7.6 -> 6.1, O and down 6.2 -> 5.6.
 template <int EPI>
 static hipError_t gemm_short(const GemmArgs& g, hipStream_t s) {
-  const int n_mt = (g.M + 15) / 16, tiles = g.N / 16, kbs = (g.K / 32 + g.ksplit - 1) / g.ksplit;
-  static constexpr int opt_mt[] = {5, 8}, opt_t[] = {1, 2, 3, 4, 6, 8, 12};
-  int mt = 5, tpw = 1;
+  const int n_mt = (g.M + 15) / 16, tiles = g.N / 16;
+  static constexpr int opt_mt[] = {2, 3, 4, 5}, opt_t[] = {1, 2, 3, 4, 6, 8, 12, 24};
+  int mt = 2, tpw = 1;
   int64_t best = INT64_MAX;
   for (int m : opt_mt)
     for (int t : opt_t) {
       const int64_t wgs = (int64_t)((tiles + t - 1) / t) * g.ksplit * ((n_mt + m - 1) / m);
-      const int64_t cost = (wgs + 255) / 256 * (1270 + 8 * (t + m) * kbs);
-      if (cost < best) {
+      const int64_t cost = (wgs + 255) / 256 * (3 * m + t);
+      if (cost <= best) {
         best = cost;
         mt = m;
         tpw = t;
@@ -530,12 +533,19 @@ static hipError_t gemm_short(const GemmArgs& g, hipStream_t s) {
     case 4: return launch_rows<M, 1, 4, 16, EPI, 4, true>(g, s);     \
     case 6: return launch_rows<M, 1, 4, 8, EPI, 6, true>(g, s);      \
     case 8: return launch_rows<M, 2, 4, 8, EPI, 4, true>(g, s);      \
-    default: return launch_rows<M, 3, 4, 4, EPI, 4, true>(g, s);     \
+    case 12: return launch_rows<M, 3, 4, 4, EPI, 4, true>(g, s);     \
+    default: return launch_rows<M, 3, 4, 4, EPI, 8, true>(g, s);     \
   }
-  if (mt == 5) {
-    FSX_SHORT(5)
+  if (mt == 2) {
+    FSX_SHORT(2)
   }
-  FSX_SHORT(8)
+  if (mt == 3) {
+    FSX_SHORT(3)
+  }
+  if (mt == 4) {
+    FSX_SHORT(4)
+  }
+  FSX_SHORT(5)
 #undef FSX_SHORT
 }
 
@@ -548,6 +558,7 @@ static hipError_t gemm_dispatch(const GemmArgs& g, hipStream_t s) {
     hipLaunchKernelGGL((k_gemm<1, EPI>), dim3((unsigned)(tiles * g.ksplit)), dim3(256), 0, s, g);
     return hipGetLastError();
   }
+  if (g.K / 32 <= SHORT_CHUNKS * 4 * g.ksplit) return gemm_short<EPI>(g, s);
   // 64 rows of the backbone, us by tiles per workgroup (3, 4, 6, 8): gate/up 46, 49, 38, 45; q/k/v 28, 31, 35, 40; O and
   // down together 45, 39, 42, 35
   const int tpw = pick_tiles(n_mt, tiles, g.K / 32, g.ksplit);
@@ -567,7 +578,6 @@ static hipError_t gemm_dispatch(const GemmArgs& g, hipStream_t s) {
       default: return launch_rows<4, 2, 4, 8, EPI, 4>(g, s);
     }
   }
-  if (g.K / 32 <= SHORT_CHUNKS * 4 * g.ksplit) return gemm_short<EPI>(g, s);
   switch (tpw) {
     case 3: return launch_rows<8, 1, 4, 8, EPI, 3>(g, s);
     case 4: return launch_rows<8, 1, 4, 8, EPI, 4>(g, s);
