@@ -586,14 +586,15 @@ static void plan_chunks(const fsx_expert* ex, TickParams& tp, int64_t rows, bool
 // Whether a tick that the persistent kernel could run is faster as one launch per phase.  The kernel takes its rows in blocks
 // of 80, each as one more round of every phase, and streams the cache of an agent of many queries through one loader wave per
 // CU; a launch per phase costs about 3 us whatever the rows.  us per tick of the full expert, kernel and phases:
-//   several query tiles per agent, 224 to 4,000 cached rows: 60 rows of tokens 1,579 to 1,678 and 1,597 to 1,692, 74 rows
-//     1,677 to 2,185 and 1,590 to 1,983, 148 rows 2,251 and 1,736, 400 rows 5,676 and 3,694;
-//   agents of one shared cache: 80 rows 1,326 and 1,546, 120 rows 2,019 and 1,636, 400 rows 5,202 and 2,279;
-//   one query tile per agent, over few cached rows: 80 rows 1,526 and 1,707, 100 rows 1,885 and 1,795, 160 rows 2,265 and
-//     1,923; the kernel streams long histories better (120 rows over 24,000 in all 3,803 and 4,283) up to two full blocks
-//     (160 rows over 16,384 in all 3,347 and 3,123, over 32,000 4,688 and 4,460).
+//   several query tiles per agent: 26 rows of tokens over 224 cached ones 1,228 and 1,218, over 4,000 1,684 and 1,530; 40 rows
+//     1,280 and 1,285, 1,722 and 1,632; 60 rows 1,503 to 1,690 and 1,291 to 1,394, 74 rows 1,677 to 2,185 and 1,432 to
+//     1,826, 148 rows 2,251 and 1,730, 400 rows 5,676 and 3,581;
+//   agents of one shared cache: 80 rows 1,326 and 1,382, 120 rows 2,019 and 1,480, 400 rows 5,202 and 2,127;
+//   one query tile per agent, over few cached rows: 80 rows 1,523 and 1,543, 100 rows 1,885 and 1,700, 160 rows 2,265 and
+//     1,939; the kernel streams long histories better (120 rows over 24,000 in all 3,790 and 4,164) up to two full blocks
+//     (160 rows over 16,384 in all 3,347 and 2,993, over 32,000 4,688 and 4,430).
 static bool phases_faster(const TickParams& tp, int64_t rows) {
-  if (tp.n_tt > 1) return tp.M > 64;
+  if (tp.n_tt > 1) return tp.M > 32 || rows >= 1024;
   if (tp.att_shared) return tp.M > 96;
   return tp.M > 144 || (tp.M > 96 && rows <= 8192);
 }

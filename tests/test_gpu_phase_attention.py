@@ -86,8 +86,9 @@ def test_agents_of_a_shared_cache_match_oracle(flags, starts_differ, frame, rows
 
 
 # agents, frame tokens, cached rows of each, shared cache, whether a launch per phase is the faster form
-ROUTES = [(2, 22, 40, False, False), (3, 12, 40, False, True), (9, 0, 40, False, False), (10, 0, 40, False, True),
-          (10, 0, 820, False, False), (15, 0, 820, False, True), (9, 0, 40, True, False), (10, 0, 40, True, True)]
+ROUTES = [(1, 22, 1023, False, False), (1, 22, 1024, False, True), (1, 23, 40, False, True), (2, 7, 40, False, True),
+          (9, 0, 40, False, False), (10, 0, 40, False, True), (10, 0, 820, False, False), (15, 0, 820, False, True),
+          (9, 0, 40, True, False), (10, 0, 40, True, True)]
 
 
 @pytest.mark.parametrize("batch,frame,rows,shared,phases", ROUTES)
