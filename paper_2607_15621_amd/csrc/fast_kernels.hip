@@ -3,10 +3,9 @@
 // One tick, per layer:
 //   qkv   : x = RMSNorm(h) (bf16) times the packed [3A][d] projection on MFMA; epilogue applies the
 //           rotary rotation to q and k and folds 1/sqrt(Dh) * log2(e) into q.
-//   attn  : split-K ("flash-decode") joint attention.  A work item is (agent, head, chunk of cached
-//           rows, tile of 16 queries); the expert's own keys/values form one extra chunk per agent, so
-//           Eq. (1)'s single softmax over [cache ; own rows] is the log-sum-exp merge of the items.
-//   comb  : merges the items of each (agent, head) and writes the attention output (bf16).
+//   attn  : split-K ("flash-decode") joint attention over chunks of cached rows, the expert's own keys/values after an
+//           agent's last chunk, so Eq. (1)'s single softmax over [cache ; own rows] is the log-sum-exp merge of the
+//           chunks, which the one that finishes last does.
 //   o     : output projection, split-K partial sums.
 //   norm  : h += sum of partials; x = RMSNorm(h) * gain (bf16) for the next projection.
 //   gu    : gate/up projection on MFMA with SwiGLU in the epilogue.
@@ -318,8 +317,8 @@ __device__ __forceinline__ void wg_barrier() {
 //
 // ALL: a K range of at most four chunks (512 columns of bf16, the expert's width), which LDS holds whole: every load is
 // issued at once.  With three buffers the last chunks waited for the first to be multiplied, and the round trips were most
-// of the expert's projections.  us for q/k/v, gate/up, O + down: 74 rows 10.9, 8.6, 13.8, now 8.5, 5.5, 9.4; 160 rows 15.2,
-// 9.8, 15.1, now 10.2, 6.1, 11.2 (with smaller row blocks too, see gemm_short).
+// of the expert's projections.  us for q/k/v, gate/up, O + down: 74 rows 10.9, 8.6, 13.8, now 8.2, 5.5, 9.7; 160 rows 15.2,
+// 9.8, 15.1, now 9.9, 5.4, 11.2 (with smaller row blocks too, see gemm_short).
 template <int MT, int NT, int KCB, int RING, int EPI, int CW, bool ALL>
 __global__ __launch_bounds__((CW + 4) * 64) void k_gemm_rows(GemmArgs g, int n_rb) {
   constexpr int CPR = KCB * 4;         // 16-byte chunks of a row in one LDS chunk
@@ -507,8 +506,8 @@ int gemm_split(int M, int N, int K) {
 // More than 16 rows over a K range that LDS holds whole: row tiles (2 to 5) and column tiles of a workgroup, by its rounds of
 // 256 workgroups times its row tiles and a third of its column tiles (the rows pass through LDS, the weights stream by
 // them).  Of the pairs below, at 74 to 400 rows of the expert, the rule picks the fastest or one within 0.5 us of it, with
-// two exceptions of 1 us.  us against row tiles of 5 and 8 weighed as much as column tiles: q/k/v of 74 rows 9.9 -> 8.5, of
-// 400 rows 23.0 -> 19.5; gate/up of 160 rows 7.6 -> 6.1, O and down 6.2 -> 5.6.
+// two exceptions of 1 us.  us against row tiles of 5 and 8 weighed as much as column tiles: q/k/v of 74 rows 9.9 -> 8.2, of
+// 400 rows 23.0 -> 18.6; gate/up of 160 rows 7.6 -> 5.4, O and down 6.2 -> 5.6.
 template <int EPI>
 static hipError_t gemm_short(const GemmArgs& g, hipStream_t s) {
   const int n_mt = (g.M + 15) / 16, tiles = g.N / 16;
@@ -630,9 +629,9 @@ hipError_t launch_gemm_down(const FastWeights& w, const TickParams& tp, const Di
 }
 
 // =====================================================================================================
-// Split-K joint attention (Eq. (1)): one wave = one work item = (agent, head, chunk of cached rows, tile of 16 queries;
-// see attn_device.h), an agent's last chunk followed by the new tokens' own rows.  The wave that finishes last among the
-// chunks of an (agent, head, query tile) merges their states in chunk order, so no launch does; an agent of one chunk
+// Split-K joint attention (Eq. (1)): one wave = one work item = (agent, head, chunk of cached rows; see
+// attn_device.h) of agents with one query tile, an agent's last chunk followed by the new tokens' own rows.  The wave that finishes last among the
+// chunks of an (agent, head) merges their states in chunk order, so no launch does; an agent of one chunk
 // writes its output at once.  Partial states cross through device-scope stores and loads, counted by a relaxed
 // device-scope atomic that the last wave resets (as k_reduce_chunks counts a row's chunks).
 // =====================================================================================================
@@ -765,28 +764,27 @@ struct AgentLanes {
 
 // The end of a work item (one wave's state of 16 queries): the output itself if the agent has one chunk, else the state to
 // its slot, and the merge by the wave that finishes last.  first, nslot: the agent's chunks; cs: this one (first <= cs).
-__device__ __forceinline__ void finish_item(const AttnArgs& a, const TickParams& tp, const AttnState& st, int b, int h, int tt,
-                                            int first, int nslot, int cs, int lane) {
-  const int rows = min(16, tp.S - tt * 16);
-  const int64_t item = ((int64_t)cs * a.H + h) * tp.n_tt + tt;
+__device__ __forceinline__ void finish_item(const AttnArgs& a, const TickParams& tp, const AttnState& st, int b, int h, int first,
+                                            int nslot, int cs, int lane) {
+  const int rows = tp.S;
+  const int64_t item = (int64_t)cs * a.H + h;
   const float lt = rows_sum(st.l);
-  uint16_t* out = a.attn_out + ((int64_t)b * tp.S + tt * 16) * a.A + (int64_t)h * a.Dh;
+  uint16_t* out = a.attn_out + (int64_t)b * tp.S * a.A + (int64_t)h * a.Dh;
   if (nslot == 1) {
     write_output(a, st, lt, rows, lane, out);
     return;
   }
   store_state(a, item, st, lt, rows, lane);
   stores_done();
-  uint32_t* cnt = a.acnt + ((int64_t)b * a.H + h) * tp.n_tt + tt;
+  uint32_t* cnt = a.acnt + (int64_t)b * a.H + h;
   uint32_t done = 0;
   if (lane == 0) done = __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   done = (uint32_t)__builtin_amdgcn_readfirstlane((int)done);
   if (done != (uint32_t)(nslot - 1)) return;
   if (lane == 0) __hip_atomic_store(cnt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   asm volatile("" ::: "memory");
-  const int64_t step = (int64_t)a.H * tp.n_tt;  // items between two chunks of the agent
   for (int qq = 0; 4 * qq < rows; ++qq)
-    merge_queries(a, (int64_t)first * step + (int64_t)h * tp.n_tt + tt, step, nslot, qq, rows, lane, out);
+    merge_queries(a, (int64_t)first * a.H + h, a.H, nslot, qq, rows, lane, out);
 }
 
 template <int KT>
@@ -794,17 +792,13 @@ __global__ __launch_bounds__(256) void k_attention(AttnArgs a, TickParams tp) {
   const int wave = wave_id(), lane = threadIdx.x & 63;
   const int item = blockIdx.x * (blockDim.x >> 6) + wave;
   if (item >= tp.n_items) return;
-  const int tt = item % tp.n_tt;
-  const int rest = item / tp.n_tt;
-  const int h = rest % a.H;
-  const int cs = rest / a.H;
+  const int h = item % a.H, cs = item / a.H;
   const AgentLanes al(tp, lane);
   const int b = __popcll(__ballot(lane < tp.B && al.prefix1 <= cs));
   const int first = al.pick(al.prefix, b), nslot = al.pick(al.prefix1, b) - first, cidx = cs - first, len = al.pick(al.len, b);
   const int grp = lane >> 4, c = lane & 15;
-  const int t = tt * 16 + c;
-  const bool tv = t < tp.S;
-  const int64_t qrow = ((int64_t)b * tp.S + (tv ? t : 0)) * a.A + (int64_t)h * a.Dh;
+  const bool tv = c < tp.S;
+  const int64_t qrow = ((int64_t)b * tp.S + (tv ? c : 0)) * a.A + (int64_t)h * a.Dh;
   uint4 qf[4];
   AttnState st;
 #pragma unroll
@@ -836,9 +830,9 @@ __global__ __launch_bounds__(256) void k_attention(AttnArgs a, TickParams tp) {
     if (KT == 1 || i0 >= i1) load_q_frag<0>(a.q, qrow, tv, grp, qf);
     const int64_t off = ((int64_t)b * tp.S * a.A + (int64_t)h * a.Dh) * 2;
     attn_rows<0, false>((const char*)a.kself + off, (const char*)a.vself + off, (int64_t)a.A * 2, 0, 0, 0, tp.S, 0, qf, 1.f,
-                        lane, st, a.causal ? tt * 16 : 1 << 30);
+                        lane, st, a.causal ? 0 : 1 << 30);
   }
-  finish_item(a, tp, st, b, h, tt, first, nslot, cs, lane);
+  finish_item(a, tp, st, b, h, first, nslot, cs, lane);
 }
 
 // The same for agents whose query tiles share their rows: several query tiles per agent, or several agents on one shared
