@@ -316,7 +316,7 @@ __device__ __forceinline__ void wg_barrier() {
 // one loader wave was the bound before (12 GB/s per CU), and operands read two at a time cost 40 % of the 512-row q/k/v.
 //
 // ALL: a K range of at most four chunks (512 columns of bf16, the expert's width), which LDS holds whole: every load is
-// issued at once.  With three buffers the last chunks waited for the first to be multiplied, and the round trips were most
+// issued at once, the chunks divided among the loaders.  With three buffers the last chunks waited for the first to be multiplied, and the round trips were most
 // of the expert's projections.  us for q/k/v, gate/up, O + down: 74 rows 10.9, 8.6, 13.8, now 8.2, 5.5, 9.7; 160 rows 15.2,
 // 9.8, 15.1, now 9.9, 5.4, 11.2 (with smaller row blocks too, see gemm_short).
 template <int MT, int NT, int KCB, int RING, int EPI, int CW, bool ALL>
@@ -324,7 +324,7 @@ __global__ __launch_bounds__((CW + 4) * 64) void k_gemm_rows(GemmArgs g, int n_r
   constexpr int CPR = KCB * 4;         // 16-byte chunks of a row in one LDS chunk
   constexpr int RPI = 64 / CPR;        // rows one direct-load instruction brings
   constexpr int NI = MT * 16 / RPI;    // instructions per chunk
-  static_assert(CPR >= 8 && CPR <= 64 && NI % 2 == 0, "chunk size");
+  static_assert(CPR >= 8 && CPR <= 64 && NI % (ALL ? 4 : 2) == 0, "chunk size");
   static_assert(RING % KCB == 0 || KCB % RING == 0, "chunk and ring sizes");
   constexpr int UN = RING > KCB ? RING : KCB;  // k-blocks per unrolled pass
   constexpr int NB = ALL ? SHORT_CHUNKS : 3;
@@ -347,37 +347,41 @@ __global__ __launch_bounds__((CW + 4) * 64) void k_gemm_rows(GemmArgs g, int n_r
     rs[threadIdx.x] = g.rscale && row < g.M ? g.rscale[row] : 1.f;
   }
   if (wave >= CW) {
-    const int par = ((wave - CW) >> 1) & 1, half = (wave - CW) & 1;
-    // this wave's half of chunk i of the rows, into buffer i % 3: row r's 16-byte chunk k at chunk position k ^ (r & 7)
-    // (the 16 rows of an operand read then fall in distinct banks); rows past M and k-blocks past the range repeat the
-    // last one
-    auto stage = [&](int i) {
+    // part of lpc of chunk i of the rows, into buffer i % NB: row r's 16-byte chunk k at chunk position k ^ (r & 7) (the 16
+    // rows of an operand read then fall in distinct banks); rows past M and k-blocks past the range repeat the last one
+    auto stage = [&](int i, int part, int lpc) {
       uint4* buf = xs[i % NB];
 #pragma unroll 8
-      for (int qq = 0; qq < NI / 2; ++qq) {
-        const int q = 2 * qq + half;
+      for (int qq = 0; qq < NI / lpc; ++qq) {
+        const int q = lpc * qq + part;
         const int r = q * RPI + lane / CPR, k = (lane % CPR) ^ (r & 7);
         const int kb = min(kb0 + i * KCB + (k >> 2), kb1 - 1);
         load_lds16<false>(g.x + (int64_t)min(row0 + r, g.M - 1) * g.ldx + kb * 32 + (k & 3) * 8, buf + q * 64);
       }
     };
-    if (par < nch) stage(par);
-    if (ALL && par + 2 < nch) stage(par + 2);
-    auto arrived = [&](int i) {  // chunk i, which this wave staged
-      if (ALL && i + 2 < nch)
-        vm_wait_below_c<NI / 2>();
-      else
-        vm_wait_all();
-    };
-    if (par == 0) arrived(0);
-    wg_barrier();
-    for (int i = 0; i + 1 < nch; ++i) {  // while chunk i is multiplied
-      if ((i & 1) == par) {
-        if (!ALL && i + 2 < nch) stage(i + 2);
-      } else {
-        arrived(i + 1);
+    const int lw = wave - CW;
+    if constexpr (ALL) {
+      // a loader has loads of one chunk only (four chunks: one loader each, two: two each), so it waits for all of its
+      // loads before the barrier of its chunk and no wait counts loads of a later one
+      const int lpc = nch > 2 ? 1 : 4 / nch, mine = lw / lpc;
+      if (mine < nch) stage(mine, lw % lpc, lpc);
+      for (int i = 0; i < nch; ++i) {
+        if (i == mine) vm_wait_all();
+        wg_barrier();
       }
+    } else {
+      const int par = lw >> 1, half = lw & 1;
+      if (par < nch) stage(par, half, 2);
+      if (par == 0) vm_wait_all();
       wg_barrier();
+      for (int i = 0; i + 1 < nch; ++i) {  // while chunk i is multiplied
+        if ((i & 1) == par) {
+          if (i + 2 < nch) stage(i + 2, half, 2);
+        } else {
+          vm_wait_all();  // chunk i + 1
+        }
+        wg_barrier();
+      }
     }
     return;
   }

@@ -61,6 +61,10 @@ CASES = {
     "single-query, 16 heads": (dict(n_frame=0, n_heads=16), 0),
     "many-query, fp8 cache": (dict(n_frame=64, n_heads=16, cache_dtype="fp8"), 0),
     "per-phase launches": (dict(n_frame=64, n_heads=16), fsx.FLAG_MULTI_LAUNCH),
+    # the projections whose rows LDS holds whole: K ranges of one to four chunks (d = 128 above), a partial last chunk
+    "per-phase, width 256": (dict(n_frame=64, n_heads=16, d_model=256), fsx.FLAG_MULTI_LAUNCH),
+    "per-phase, width 352": (dict(n_frame=64, n_heads=16, d_model=352), fsx.FLAG_MULTI_LAUNCH),
+    "per-phase, width 512": (dict(n_frame=64, n_heads=16, d_model=512), fsx.FLAG_MULTI_LAUNCH),
     "generic path": (dict(n_frame=64, n_heads=4), fsx.FLAG_GENERIC),
 }
 
