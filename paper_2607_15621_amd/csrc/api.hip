@@ -519,6 +519,8 @@ size_t static_phase_layout(const fsx_expert* ex, const TickParams& tp, char* bas
 }
 }  // namespace
 
+constexpr int ATT_WAVES = 2048;  // waves of the per-phase attention that 256 CUs hold at once, eight each
+
 // Split plan of the per-phase attention.
 static void plan_chunks(const fsx_expert* ex, TickParams& tp, int64_t rows, bool shared) {
   const int H = ex->cfg.n_heads;
@@ -567,8 +569,8 @@ static void plan_chunks(const fsx_expert* ex, TickParams& tp, int64_t rows, bool
     return;
   }
   // One wave per work item: chunks of chunk_rows cached rows (a multiple of 32) so that the items (chunk, head, query
-  // tile) number about 2048, eight waves per CU, and fit the workspace.
-  const int64_t work = rows * H * tp.n_tt, target = 2048;
+  // tile) number about ATT_WAVES and fit the workspace.
+  const int64_t work = rows * H * tp.n_tt, target = ATT_WAVES;
   int64_t cr = std::max<int64_t>(32, ((work + target - 1) / target + 31) / 32 * 32);
   for (;; cr *= 2) {
     tp.chunk_prefix[0] = 0;
@@ -585,18 +587,42 @@ static void plan_chunks(const fsx_expert* ex, TickParams& tp, int64_t rows, bool
 
 // Whether a tick that the persistent kernel could run is faster as one launch per phase.  The kernel takes its rows in blocks
 // of 80, each as one more round of every phase, and streams the cache of an agent of many queries through one loader wave per
-// CU; a launch per phase costs about 3 us whatever the rows.  us per tick of the full expert, kernel and phases:
-//   several query tiles per agent: 26 rows of tokens over 224 cached ones 1,228 and 1,218, over 4,000 1,684 and 1,530; 40 rows
-//     1,280 and 1,285, 1,722 and 1,632; 60 rows 1,503 to 1,690 and 1,291 to 1,394, 74 rows 1,677 to 2,185 and 1,432 to
-//     1,826, 148 rows 2,251 and 1,730, 400 rows 5,676 and 3,581;
-//   agents of one shared cache: 80 rows 1,326 and 1,382, 120 rows 2,019 and 1,480, 400 rows 5,202 and 2,127;
-//   one query tile per agent, over few cached rows: 80 rows 1,523 and 1,543, 100 rows 1,885 and 1,700, 160 rows 2,265 and
-//     1,939; the kernel streams long histories better (120 rows over 24,000 in all 3,790 and 4,164) up to two full blocks
-//     (160 rows over 16,384 in all 3,347 and 2,993, over 32,000 4,688 and 4,430).
-static bool phases_faster(const TickParams& tp, int64_t rows) {
-  if (tp.n_tt > 1) return tp.M > 32 || rows >= 1024;
-  if (tp.att_shared) return tp.M > 96;
-  return tp.M > 144 || (tp.M > 96 && rows <= 8192);
+// CU; a launch per phase costs about 3 us whatever the rows, and one wave per chunk streams long histories more slowly than
+// the kernel's rings.  us per tick, kernel and phases, of the full expert (32 layers of 32 heads); the other widths and
+// head counts measured (8 layers of 256 and 8 heads, 16 of 512 and 16, 4 of 128 and 4) keep within 4 % of the faster form
+// on the phases' side of the lines that bound it, their cached rows counted by heads.
+//   agents of one shared cache: 80 rows of tokens 1,326 and 1,382, 120 rows 2,019 and 1,480, 400 rows 5,202 and 2,127; over
+//     16,000 rows 120 rows 8,450 and 4,149 (fp8 7,175 and 5,264).
+//   several query tiles per agent: 26 rows over 224 cached ones 1,228 and 1,218, over 4,000 1,684 and 1,530; 60 rows 1,503
+//     to 1,690 and 1,291 to 1,394, 148 rows 2,251 and 1,730, 400 rows 5,676 and 3,581.  One agent of three tiles has
+//     workgroups for few heads only: 40 rows over 24 cached ones 1,153 and 1,259, over 224 1,271 and 1,290, over 500 1,460
+//     and 1,336; with 16 heads 573 and 553 over 24.  Two tiles over fp8 rows, which two waves of a workgroup decode: 30 rows
+//     over 12,000 2,212 and 2,167, over 20,000 2,707 and 2,755; 64 rows over 24,000 3,104 and 3,082, over 40,000 4,109 and
+//     4,280; 120 rows over 16,000 2,932 and 2,627, over 64,000 5,928 and 6,325; 416 rows over 64,000 9,088 and 7,120, over
+//     256,000 20,780 and 21,880.  Three tiles and more, and bf16 rows: the phases at every length.
+//   one query tile per agent: 80 rows 1,523 and 1,543, 100 rows 1,885 and 1,700.  Beyond 96 rows the line lies at the length
+//     where the rounds of the chain that the phases save are used up by their slower streaming.  That is slowest where the
+//     attention's waves exceed one round of eight per CU, which equal shares of 16, 32 or 64 agents do not: 150 rows over
+//     15,000 bf16 rows 3,334 and 2,794, over 30,000 4,727 and 4,966, over 120,000 12,307 and 14,365; fp8 over 30,000 3,581
+//     and 3,397, over 60,000 4,923 and 5,290, over 240,000 12,457 and 15,916; 320 rows in uneven histories over 32,512 bf16
+//     rows 6,248 and 5,770, over 65,008 8,921 and 9,199, fp8 6,753 and 6,318, over 130,000 9,359 and 10,295; 640 rows (40
+//     agents) over 160,000 18,137 and 19,486, fp8 11,898 and 12,665.  In one round: 160 rows over 192,000 bf16 rows 17,978
+//     and 17,677, fp8 over 64,000 4,967 and 4,933, over 256,000 13,079 and 14,360; 320 rows over 256,000 fp8 rows 14,162 and
+//     14,933.
+static bool phases_faster(const TickParams& tp, const Dims& dm, int64_t rows, bool fp8) {
+  const int64_t load = rows * dm.H / 32;  // cached rows of 32 heads
+  if (tp.n_tt > 1) {
+    if (tp.M <= 32 && rows < 1024) return false;
+    if (tp.n_tt > 2 && tp.M <= 48 && dm.H > 16 && rows < 224) return false;
+    if (!fp8 || tp.n_tt > 2 || tp.att_shared) return true;
+    return load <= (tp.M <= 48 ? 12000 : (tp.M <= 80 ? 24000 : (tp.M <= 320 ? 40000 : 150000)));
+  }
+  if (tp.M <= 96) return false;
+  if (tp.att_shared) return true;
+  if (tp.M <= 144) return rows <= 8192;
+  const int64_t blocks = (tp.M + 79) / 80;
+  if (tp.n_items <= ATT_WAVES) return !fp8 || load <= 30000 * blocks;
+  return load <= std::min<int64_t>((fp8 ? 32000 : 16000) * (blocks - 1), 110000);
 }
 
 static int forward_impl(fsx_expert* ex, const fsx_cache_desc* cache, const void* tokens, int32_t batch,
@@ -670,9 +696,10 @@ static int forward_impl(fsx_expert* ex, const fsx_cache_desc* cache, const void*
     // partial-state slots per XCD: at most one per segment (<= 4 local heads per agent) plus one per slice boundary
     // (the kernel checks the bound and fails the tick if the placement breaks it)
     tp.slot_x = batch * 4 + (use_static ? ex->wg_per_xcd_max : G);
-    if (phases_faster(tp, rows) && !(c.flags & FSX_FLAG_TRACE)) {
-      // Both entry points take the same path, so that their results are the same: phases, if the static array holds their
-      // workspace, or if it does not hold the kernel's either (the allocation-free entry point then refuses the call).
+    if (phases_faster(tp, dm, rows, cv.dtype == FSX_FP8_E4M3) && !(c.flags & FSX_FLAG_TRACE)) {
+      // Both entry points take the same path, so that their results are the same: phases, unless the static array holds the
+      // kernel's workspace and not theirs.  The allocation-free entry point refuses a call whose kernel workspace it does not
+      // hold, whichever path the other takes.
       TickParams st = tp;
       st.slot_x = batch * 4 + ex->wg_per_xcd_max;
       TickArgs dummy = ex->ta;

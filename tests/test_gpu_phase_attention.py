@@ -85,6 +85,30 @@ def test_agents_of_a_shared_cache_match_oracle(flags, starts_differ, frame, rows
     ex.close()
 
 
+def check_route(wl, make_desc, phases, what):
+    """The default handle takes the faster form, bit for bit, and so does the allocation-free entry point."""
+    model = Model(wl)
+    desc = make_desc()
+    host_tok, tok = tokens_for(wl)
+    shapes = (wl.batch, wl.n_out), (wl.n_layers, wl.batch, wl.seq, wl.d_model)
+    got = {}
+    for name, flags in (("default", 0), ("phases", fsx.FLAG_MULTI_LAUNCH), ("kernel", fsx.FLAG_TRACE)):
+        ex = model.create(flags=flags)
+        calls = [(name, fsx.expert_forward)] + ([("noalloc", fsx.expert_forward_noalloc)] if name == "default" else [])
+        for key, call in calls:
+            wp, hid = (torch.full(s, float("nan"), device="cuda") for s in shapes)
+            call(ex, desc, tok, wl.batch, wl.n_frame_tokens, wp, hid)
+            torch.cuda.synchronize()
+            got[key] = wp.cpu().numpy(), hid.cpu().numpy()
+        ex.close()
+    same = lambda a, b: all(np.array_equal(x, y) for x, y in zip(got[a], got[b]))  # noqa: E731
+    assert not same("phases", "kernel"), "the two forms agree bitwise: the test could not tell them apart"
+    assert same("default", "phases" if phases else "kernel"), what
+    assert same("noalloc", "default")
+    for x, y in zip(got["phases"], got["kernel"]):
+        assert rel_err(x, y) <= TOL
+
+
 # agents, frame tokens, cached rows of each, shared cache, whether a launch per phase is the faster form
 ROUTES = [(1, 22, 1023, False, False), (1, 22, 1024, False, True), (1, 23, 40, False, True), (2, 7, 40, False, True),
           (9, 0, 40, False, False), (10, 0, 40, False, True), (10, 0, 820, False, False), (15, 0, 820, False, True),
@@ -93,28 +117,38 @@ ROUTES = [(1, 22, 1023, False, False), (1, 22, 1024, False, True), (1, 23, 40, F
 
 @pytest.mark.parametrize("batch,frame,rows,shared,phases", ROUTES)
 def test_route_of_a_tick_by_its_rows(batch, frame, rows, shared, phases):
-    """The default handle takes the faster form on both sides of every line, and so does the allocation-free entry point."""
+    """Both sides of every line over the rows of tokens."""
     print(f"case route {batch} {frame} {rows} {shared}", flush=True)
     wl = workload("phroute", 790, (rows,) * batch, frame, heads=2)
-    model = Model(wl)
     cache = Cache(wl.replace(batch=1, lengths=(rows,)) if shared else wl)
     if shared:
         cache.desc = fsx.CacheDesc(cache.k, cache.v, fsx.BF16, wl.n_layers, wl.n_heads, wl.head_dim, wl.capacity,
                                    [rows] * batch, positions=[rows] * batch, layout=fsx.CACHE_SHARED)
-    host_tok, tok = tokens_for(wl)
-    got = {}
-    for name, flags in (("default", 0), ("phases", fsx.FLAG_MULTI_LAUNCH), ("kernel", fsx.FLAG_TRACE)):
-        ex = model.create(flags=flags)
-        got[name] = run_forward(ex, cache, tok, batch, frame, with_hidden=True)
-        if name == "default":
-            wp = torch.full((batch, wl.n_out), float("nan"), device="cuda")
-            hid = torch.full((wl.n_layers, batch, wl.seq, wl.d_model), float("nan"), device="cuda")
-            fsx.expert_forward_noalloc(ex, cache.desc, tok, batch, frame, wp, hid)
-            torch.cuda.synchronize()
-            got["noalloc"] = wp.cpu().numpy(), hid.cpu().numpy()
-        ex.close()
-    same = lambda a, b: all(np.array_equal(x, y) for x, y in zip(got[a], got[b]))  # noqa: E731
-    assert not same("phases", "kernel"), "the two forms agree bitwise: the test could not tell them apart"
-    assert same("default", "phases" if phases else "kernel") and same("noalloc", "default")
-    for x, y in zip(got["phases"], got["kernel"]):
-        assert rel_err(x, y) <= TOL
+    check_route(wl, lambda: cache.desc, phases, "the other form was taken")
+
+
+# agents, frame tokens, cached rows of each, fp8 cache, whether a launch per phase is the faster form: 32 heads, histories on
+# both sides of where the kernel's streaming makes up for its rounds
+LONG_ROUTES = [(15, 0, 1066, False, True), (15, 0, 1067, False, False), (15, 0, 2133, True, True), (15, 0, 2134, True, False),
+               (16, 0, 3751, False, True), (16, 0, 3750, True, True), (16, 0, 3751, True, False),
+               (1, 22, 12000, True, True), (1, 22, 12001, True, False), (1, 22, 12001, False, True),
+               (1, 30, 223, False, False), (1, 30, 224, False, True)]
+
+
+@pytest.mark.parametrize("batch,frame,rows,fp8,phases", LONG_ROUTES)
+def test_route_of_a_tick_by_its_history(batch, frame, rows, fp8, phases):
+    print(f"case route of 32 heads {batch} {frame} {rows} {fp8}", flush=True)
+    wl = workload("phlong", 791, (rows,) * batch, frame, "fp8" if fp8 else "bf16", heads=32)
+    shape = (batch, wl.n_layers, wl.n_heads, wl.capacity, wl.head_dim)
+    g = torch.Generator(device="cuda").manual_seed(791)
+
+    def desc():
+        k, v = (torch.randn(shape, generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+        if not fp8:
+            return fsx.CacheDesc(k, v, fsx.BF16, wl.n_layers, wl.n_heads, wl.head_dim, wl.capacity, wl.lengths)
+        k, v = (x.to(torch.float8_e4m3fn).view(torch.uint8) for x in (k, v))
+        ones = torch.ones(shape[:3], device="cuda")
+        return fsx.CacheDesc(k, v, fsx.FP8_E4M3, wl.n_layers, wl.n_heads, wl.head_dim, wl.capacity, wl.lengths, k_scale=ones,
+                             v_scale=ones)
+
+    check_route(wl, desc, phases, "the other form was taken")
