@@ -194,7 +194,7 @@ def test_whole_range_units_on_power_of_two_rings_match_oracle(cache_dtype, n_fra
                         cache_dtype=cache_dtype, capacity=128)
     say(f"case whole-range units, {cache_dtype}, {n_frame} frame tokens, capacity 128")
     model = Model(wl)
-    ex = model.create()
+    ex = model.create(flags=fsx.FLAG_TRACE)  # the tick kernel
     cache = Cache(wl, starts=(120, 64, 0, 127))
     host_tok, tok = tokens_for(wl)
     wp, _ = run_forward(ex, cache, tok, wl.batch, n_frame)
@@ -219,7 +219,7 @@ def test_stress_keys_rescale_within_a_range_match_oracle(cache_dtype, n_frame):
         n_frame_tokens=n_frame, stress_keys=True)
     say(f"case stress keys, {cache_dtype}, {n_frame} frame tokens")
     model = Model(wl)
-    ex = model.create()
+    ex = model.create(flags=fsx.FLAG_TRACE)  # the tick kernel
     cache = Cache(wl, starts=(15, 700, 0))
     host_tok, tok = tokens_for(wl)
     wp, _ = run_forward(ex, cache, tok, wl.batch, n_frame)
@@ -238,7 +238,7 @@ def test_small_fp8_cache_with_frame_tokens_matches_oracle(n_frame):
     wl = small(62, lengths=(290, 64), capacity=300, cache_dtype="fp8").replace(n_frame_tokens=n_frame)
     say(f"case small fp8 with {n_frame} frame tokens")
     model = Model(wl)
-    ex = model.create()
+    ex = model.create(flags=fsx.FLAG_TRACE)  # the tick kernel
     cache = Cache(wl, starts=(250, 7))
     host_tok, tok = tokens_for(wl)
     wp, _ = run_forward(ex, cache, tok, wl.batch, wl.n_frame_tokens)
@@ -257,7 +257,7 @@ def test_fp8_many_query_slices_across_agents_match_oracle():
                         cache_dtype="fp8", capacity=3200)
     say("case fp8 many-query slices")
     model = Model(wl)
-    ex = model.create()
+    ex = model.create(flags=fsx.FLAG_TRACE)  # the tick kernel
     cache = Cache(wl, starts=(3100, 5, 700))
     host_tok, tok = tokens_for(wl)
     wp, _ = run_forward(ex, cache, tok, wl.batch, wl.n_frame_tokens)

@@ -8,7 +8,8 @@ oracle cannot see such races when they only perturb the last bits (near-uniform 
 a wrong query row almost entirely), so these tests compare launches with each other, bit for bit.
 
 Cases: the many-query attention (64 frame tokens, five query tiles per agent) with one and with two heads per XCD,
-the single-query attention of 16 heads, the fp8 cache, and the per-phase launches and the generic path.
+the single-query attention of 16 heads, the fp8 cache, and the per-phase launches and the generic path.  The many-query
+cases of the tick kernel force it by tracing (a default handle runs them as a launch per phase).
 
 The alternating-inputs test runs two token sets in turn on one handle and requires each launch to reproduce the
 first result of its own set, bit for bit: nothing a launch leaves in the workspace (flags, stamped words, partial
@@ -54,12 +55,12 @@ def launch(ex, cache, tok, wl):
 
 
 CASES = {
-    "width 512, many-query": (dict(n_frame=64, n_heads=8, d_model=512), 0),
+    "width 512, many-query": (dict(n_frame=64, n_heads=8, d_model=512), fsx.FLAG_TRACE),
     "width 512, single-query": (dict(n_frame=0, n_heads=8, d_model=512), 0),
-    "many-query, 1 head per XCD": (dict(n_frame=64, n_heads=4), 0),
-    "many-query, 2 heads per XCD": (dict(n_frame=64, n_heads=16), 0),
+    "many-query, 1 head per XCD": (dict(n_frame=64, n_heads=4), fsx.FLAG_TRACE),
+    "many-query, 2 heads per XCD": (dict(n_frame=64, n_heads=16), fsx.FLAG_TRACE),
     "single-query, 16 heads": (dict(n_frame=0, n_heads=16), 0),
-    "many-query, fp8 cache": (dict(n_frame=64, n_heads=16, cache_dtype="fp8"), 0),
+    "many-query, fp8 cache": (dict(n_frame=64, n_heads=16, cache_dtype="fp8"), fsx.FLAG_TRACE),
     "per-phase launches": (dict(n_frame=64, n_heads=16), fsx.FLAG_MULTI_LAUNCH),
     # the projections whose rows LDS holds whole: K ranges of one to four chunks (d = 128 above), a partial last chunk
     "per-phase, width 256": (dict(n_frame=64, n_heads=16, d_model=256), fsx.FLAG_MULTI_LAUNCH),
@@ -90,14 +91,14 @@ def test_repeated_launches_are_bit_identical(case):
     assert not differ, f"launches differ from the first (run, [(agent, query tile)]): {differ}"
 
 
-@pytest.mark.parametrize("n_frame", [0, 64])
-def test_alternating_inputs_reproduce_their_results(n_frame):
+@pytest.mark.parametrize("n_frame,flags", [(0, 0), (64, fsx.FLAG_TRACE), (64, 0)])
+def test_alternating_inputs_reproduce_their_results(n_frame, flags):
     wl = small(720 + n_frame, n_frame=n_frame, n_heads=8, d_model=512)
     say(f"case alternating inputs: width 512, {n_frame} frame tokens")
     model = Model(wl)
     cache = Cache(wl, starts=(100, 0, 310))
     toks = [tokens_for(wl)[1], tokens_for(dataclasses.replace(wl, wid=wl.wid + 1000))[1]]
-    ex = model.create()
+    ex = model.create(flags=flags)
     first = [launch(ex, cache, toks[0], wl), launch(ex, cache, toks[1], wl)]
     assert not np.array_equal(first[0][0], first[1][0]), "the two token sets give the same waypoints"
     differ = []

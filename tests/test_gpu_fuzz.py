@@ -3,7 +3,7 @@
 Each case draws its configuration from its own seed (so a failure names a reproducible shape): 1-3 layers, width
 128-512, 4-32 heads of 128, SwiGLU width 256-2048, 8-16 expert tokens, 0-70 frame tokens (one to six query tiles),
 1-6 agents with lengths 0-400 (some empty) on rings that wrap at random rows, a bf16 or fp8 cache in either layout,
-and the persistent tick kernel or the per-phase launches.  The shapes stay inside what the tick kernel takes (at
+and the persistent tick kernel (forced by tracing) or the per-phase launches.  The shapes stay inside what the tick kernel takes (at
 most 4 heads and 512 FFN columns per XCD).
 """
 
@@ -46,7 +46,7 @@ def draw(case: int):
         n_frame_tokens=int(rng.choice([0, 0, 7, 30, 70])), batch=B, lengths=tuple(lengths), dtype="bf16",
         cache_dtype=str(rng.choice(["bf16", "fp8"])), capacity=capacity)
     layout = fsx.CACHE_TOKEN_MAJOR if rng.random() < 0.5 else fsx.CACHE_HEAD_MAJOR
-    flags = fsx.FLAG_MULTI_LAUNCH if rng.random() < 0.3 else 0
+    flags = fsx.FLAG_MULTI_LAUNCH if rng.random() < 0.3 else fsx.FLAG_TRACE
     return wl, starts, layout, flags
 
 
@@ -55,7 +55,7 @@ def test_draws_cover_the_intended_space():
     cases = [draw(c) for c in range(N_CASES)]
     assert any(wl.cache_dtype == "fp8" for wl, *_ in cases) and any(wl.cache_dtype == "bf16" for wl, *_ in cases)
     assert any(lay == fsx.CACHE_TOKEN_MAJOR for _, _, lay, _ in cases)
-    assert any(fl == fsx.FLAG_MULTI_LAUNCH for *_, fl in cases) and any(fl == 0 for *_, fl in cases)
+    assert any(fl == fsx.FLAG_MULTI_LAUNCH for *_, fl in cases) and any(fl == fsx.FLAG_TRACE for *_, fl in cases)
     assert any(wl.seq > 16 for wl, *_ in cases) and any(wl.seq <= 16 for wl, *_ in cases)
     assert any(0 in wl.lengths for wl, *_ in cases)
 
@@ -67,7 +67,7 @@ def test_random_shape_matches_oracle(case):
         f"T {wl.n_expert_tokens}, F {wl.n_frame_tokens}, lengths {list(wl.lengths)}, capacity {wl.capacity}, "
         f"starts {starts}, cache {wl.cache_dtype}, "
         f"{'token' if layout == fsx.CACHE_TOKEN_MAJOR else 'head'}-major, "
-        f"{'per-phase' if flags else 'tick kernel'}")
+        f"{'per-phase' if flags == fsx.FLAG_MULTI_LAUNCH else 'tick kernel'}")
     model = Model(wl)
     ex = model.create(flags=flags)
     cache = Cache(wl, starts=starts, layout=layout)

@@ -98,7 +98,7 @@ def test_appended_ring_equals_bulk_written_ring(layout, capacity):
 @pytest.mark.parametrize("path", ["tick", "per-phase", "generic"])
 @pytest.mark.parametrize("n_frame", [0, 64])
 def test_token_major_cache_matches_oracle(path, n_frame):
-    flags = {"tick": 0, "per-phase": fsx.FLAG_MULTI_LAUNCH, "generic": fsx.FLAG_GENERIC}[path]
+    flags = {"tick": fsx.FLAG_TRACE, "per-phase": fsx.FLAG_MULTI_LAUNCH, "generic": fsx.FLAG_GENERIC}[path]
     wl = small(210 + n_frame, lengths=(300, 0, 77), capacity=320, n_frame=n_frame, n_heads=16)
     say(f"case token-major {path} n_frame={n_frame}")
     model = Model(wl)
@@ -159,7 +159,7 @@ def test_token_major_append_is_bit_exact():
 def test_expert_without_rotary_encoding_matches_oracle(path, n_frame):
     """rope_base = 0: learned positional embeddings are part of the input tokens, the expert's q and k are not
     rotated (Sec. 3.1)."""
-    flags = {"tick": 0, "per-phase": fsx.FLAG_MULTI_LAUNCH}[path]
+    flags = {"tick": fsx.FLAG_TRACE, "per-phase": fsx.FLAG_MULTI_LAUNCH}[path]
     wl = small(240 + n_frame, lengths=(150, 257), capacity=300, n_frame=n_frame, n_heads=16, rope_base=0.0)
     say(f"case no rotary {path} n_frame={n_frame}")
     model = Model(wl)

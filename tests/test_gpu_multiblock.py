@@ -26,10 +26,12 @@ def say(*a):
     sys.stdout.flush()
 
 
+@pytest.mark.parametrize("flags", [0, fsx.FLAG_TRACE])  # a launch per phase, and the tick kernel
 @pytest.mark.parametrize("layout", [fsx.CACHE_HEAD_MAJOR, fsx.CACHE_TOKEN_MAJOR])
 @pytest.mark.parametrize("delta,rope,n_layers,d_model,n_heads", [(2, 0.0, 2, 256, 16), (0, 10000.0, 2, 256, 16),
                                                                  (2, 0.0, 3, 512, 32)])
-def test_clip_blocks_over_shared_cache_match_masked_oracle(layout, delta, rope, n_layers, d_model, n_heads):
+def test_clip_blocks_over_shared_cache_match_masked_oracle(layout, delta, rope, n_layers, d_model, n_heads,
+                                                                 flags):
     n_text, per, J = 64, 4, 12
     L = n_text + per * J
     vis = oracle.staleness_visible_rows(n_text, per, J, delta)
@@ -42,7 +44,7 @@ def test_clip_blocks_over_shared_cache_match_masked_oracle(layout, delta, rope, 
     desc = fsx.CacheDesc(one.k, one.v, fsx.BF16, wl.n_layers, wl.n_heads, wl.head_dim, L, vis, positions=vis,
                          layout=layout | fsx.CACHE_SHARED)
     host_tok, tok = tokens_for(wl)
-    ex = model.create()
+    ex = model.create(flags=flags)
     wp = torch.full((J, wl.n_out), float("nan"), device="cuda")
     hid = torch.full((wl.n_layers, J, wl.seq, wl.d_model), float("nan"), device="cuda")
     fsx.expert_forward(ex, desc, tok, J, 0, wp, hid)

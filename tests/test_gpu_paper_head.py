@@ -40,7 +40,7 @@ def folded_tokens(wl):
 @pytest.mark.parametrize("path", ["tick", "per-phase", "generic"])
 @pytest.mark.parametrize("n_frame", [0, 30])
 def test_paper_form_small_matches_oracle(path, n_frame):
-    flags = {"tick": 0, "per-phase": fsx.FLAG_MULTI_LAUNCH, "generic": fsx.FLAG_GENERIC}[path]
+    flags = {"tick": fsx.FLAG_TRACE, "per-phase": fsx.FLAG_MULTI_LAUNCH, "generic": fsx.FLAG_GENERIC}[path]
     wl = paper_form(synth.Workload(name="paper_small", wid=500 + n_frame, n_layers=2, d_model=256, n_heads=16,
                                    head_dim=128, d_ffn=512, n_expert_tokens=10, n_frame_tokens=n_frame, batch=3,
                                    lengths=(200, 0, 77), dtype="bf16", cache_dtype="bf16", capacity=256), hidden=256)
@@ -106,7 +106,7 @@ def test_query_head_at_the_edges_of_its_split(path, d, hidden, n_out, tokens, ba
                                    n_out=n_out), hidden=hidden)
     say(f"case query head {path} d={d} hidden={hidden} n_out={n_out} batch={batch}")
     model = Model(wl)
-    ex = model.create(flags={"tick": 0, "per-phase": fsx.FLAG_MULTI_LAUNCH, "generic": fsx.FLAG_GENERIC}[path])
+    ex = model.create(flags={"tick": fsx.FLAG_TRACE, "per-phase": fsx.FLAG_MULTI_LAUNCH, "generic": fsx.FLAG_GENERIC}[path])
     _, tok = folded_tokens(wl)
     wp, hid = run_forward(ex, Cache(wl), tok, batch, 0, with_hidden=True)
     h, nq = model.head_w, n_out // 2

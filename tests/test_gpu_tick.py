@@ -1,4 +1,5 @@
-"""The persistent tick kernel: agreement with the per-phase launch path, consecutive ticks with new inputs,
+"""The persistent tick kernel (tests of many rows, which a default handle runs as a launch per phase, force it by
+tracing): agreement with the per-phase launch path, consecutive ticks with new inputs,
 per-layer hidden outputs, and the bounded-wait failure path (forced from the host by a tiny wait limit)."""
 
 from __future__ import annotations
@@ -39,7 +40,7 @@ def test_tick_kernel_and_per_phase_launches_match_oracle(n_frame):
     cache = Cache(wl, starts=(390, 0, 200, 1))
     host_tok, tok = tokens_for(wl)
     outs = {}
-    for name, flags in (("tick", 0), ("per-phase", fsx.FLAG_MULTI_LAUNCH)):
+    for name, flags in (("tick", fsx.FLAG_TRACE), ("per-phase", fsx.FLAG_MULTI_LAUNCH)):
         ex = model.create(flags=flags)
         wp, hid = run_forward(ex, cache, tok, wl.batch, n_frame, with_hidden=True)
         outs[name] = (wp, hid)
@@ -51,6 +52,7 @@ def test_tick_kernel_and_per_phase_launches_match_oracle(n_frame):
             record(b, max(rel_err(hid[l, b], ref_hid[l]) for l in range(wl.n_layers)), TOL,
                    what=f"{name} worst layer hidden, max|d| / max|ref|")
     assert rel_err(outs["tick"][0], outs["per-phase"][0]) <= 1e-2
+    assert not np.array_equal(outs["tick"][1], outs["per-phase"][1]), "the two forms agree bitwise: one was compared with itself"
 
 
 @pytest.mark.parametrize("lengths", [(150,), (0,), (333,)])
@@ -102,7 +104,7 @@ def test_maximum_batch_of_agents_matches_oracle():
     model = Model(wl)
     cache = Cache(wl, starts=tuple(int(x) for x in rng.integers(0, 128, 64)))
     host_tok, tok = tokens_for(wl)
-    ex = model.create()
+    ex = model.create(flags=fsx.FLAG_TRACE)
     wp, _ = run_forward(ex, cache, tok, wl.batch, 0)
     pos = [int(p) for p in cache.desc.pos]
     refs = oracle_agents(model, range(wl.batch),
@@ -123,7 +125,7 @@ def test_many_query_slices_across_agents_match_oracle(n_frame):
     model = Model(wl)
     cache = Cache(wl, starts=(3000, 17, 900))
     host_tok, tok = tokens_for(wl)
-    ex = model.create()
+    ex = model.create(flags=fsx.FLAG_TRACE)
     wp, _ = run_forward(ex, cache, tok, wl.batch, n_frame)
     for b in range(wl.batch):
         ref, _ = model.oracle_agent(host_tok[b], cache.oracle_rows(b), cache.desc.pos[b])

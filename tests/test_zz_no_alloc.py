@@ -42,10 +42,11 @@ def noalloc_forward(ex, cache, tok, batch, n_frame, with_hidden=True):
     return wp.cpu().numpy(), (hid.cpu().numpy() if with_hidden else None)
 
 
-def test_noalloc_tick_matches_forward_on_two_calls():
+@pytest.mark.parametrize("flags", [0, fsx.FLAG_TRACE])  # the larger call as a launch per phase, and in the tick kernel
+def test_noalloc_tick_matches_forward_on_two_calls(flags):
     big = wl_of(300, lengths=(600, 37, 250), n_frame=30)
     model = Model(big)
-    ex = model.create(max_batch=3, max_frame_tokens=30)
+    ex = model.create(max_batch=3, max_frame_tokens=30, flags=flags)
     calls = [(big, (5, 0, 300)), (wl_of(301, lengths=(120,), n_frame=0), (100,))]
     for i, (wl, starts) in enumerate(calls):
         say(f"case noalloc call {i}: {wl.batch} agents, {wl.n_frame_tokens} frame tokens, L={wl.lengths}")
