@@ -95,7 +95,8 @@ typedef struct {
   int32_t flags;            /* FSX_FLAG_* */
   int32_t tick_timeout_us;  /* bound on any wait inside the tick kernel; 0 = 2 s */
   int32_t head_kind;        /* FSX_HEAD_MEAN_LINEAR or FSX_HEAD_QUERY_MLP */
-  int32_t head_hidden;      /* FSX_HEAD_QUERY_MLP: width of the head's hidden layer, 1..2048; ignored otherwise */
+  int32_t head_hidden;      /* FSX_HEAD_QUERY_MLP: width of the head's hidden layer, 1..2048, with n_out / 2 *
+                               (d_model + head_hidden) at most 16384 (FSX_E_UNSUPPORTED beyond); ignored otherwise */
 } fsx_expert_cfg;
 
 /* Waypoint heads (fsx_expert_cfg.head_kind). */

@@ -94,8 +94,9 @@ static int validate_cfg(const fsx_expert_cfg* c) {
     if (c->n_out % 2 || c->n_out / 2 > c->n_expert_tokens || c->n_out / 2 > QH_MAX_QUERIES)
       return fail(FSX_E_INVALID, "the query head needs an even n_out with n_out / 2 <= min(n_expert_tokens, 8)");
     if (c->head_hidden < 1 || c->head_hidden > 2048) return fail(FSX_E_INVALID, "head_hidden must be in 1..2048");
-    if ((int64_t)(c->n_out / 2) * (c->d_model + c->head_hidden) * 4 > 64 * 1024)
-      return fail(FSX_E_UNSUPPORTED, "query head rows and hidden activations beyond 64 KiB of LDS");
+    // The head's LDS (n_out / 2 rows of d_model + 256 floats, see query_head_part) is then at most 72 KiB, of a workgroup's 160.
+    if ((int64_t)(c->n_out / 2) * (c->d_model + c->head_hidden) > 16384)
+      return fail(FSX_E_UNSUPPORTED, "the query head takes n_out / 2 * (d_model + head_hidden) of at most 16384");
   }
   return FSX_OK;
 }

@@ -58,3 +58,14 @@ def test_cache_layout_is_validated_before_any_gpu_work():
     assert fsx.lib().fsx_cache_append_rows(ctypes.byref(desc.c), None, None, 4, 0, None) == 1
     assert "layout" in fsx.last_error()
     assert fsx.lib().fsx_probe_hbm_read(None, 16, 0, None, None) == 1
+
+
+def test_query_head_limit_is_the_one_its_message_names():
+    """n_out / 2 rows of d_model + head_hidden, at most 16384 in all: on both sides of it (eight queries of width 1900)."""
+    out = ctypes.c_void_p(0)
+    codes = {}
+    for hidden in (148, 149):
+        cfg = fsx.make_cfg(1, 1900, 8, 128, 256, n_out=16, head_kind=fsx.HEAD_QUERY_MLP, head_hidden=hidden)
+        codes[hidden] = fsx.lib().fsx_expert_create(ctypes.byref(cfg), None, None, None, None, ctypes.byref(out)), fsx.last_error()
+    assert codes[148][0] == 1 and "layers" in codes[148][1]  # the sizes are accepted, the missing layers are not
+    assert codes[149][0] == 2 and "at most 16384" in codes[149][1] and "LDS" not in codes[149][1]
