@@ -158,14 +158,6 @@ __device__ __forceinline__ void st_dev(uint64_t* p, uint64_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ void st_dev_f(float* p, float v) { st_dev(reinterpret_cast<uint32_t*>(p), __float_as_uint(v)); }
-__device__ __forceinline__ void st_dev16(void* p, uint4 v) {
-  uint64_t* q = reinterpret_cast<uint64_t*>(p);
-  st_dev(q, (uint64_t)v.x | ((uint64_t)v.y << 32));
-  st_dev(q + 1, (uint64_t)v.z | ((uint64_t)v.w << 32));
-}
-__device__ __forceinline__ void st_dev_f4(float* p, float4 v) {
-  st_dev16(p, make_uint4(__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w)));
-}
 __device__ __forceinline__ uint32_t ld_dev(const uint32_t* p) {
   return __hip_atomic_load(const_cast<uint32_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }

@@ -126,7 +126,7 @@ hipError_t launch_embed(const void* tokens, int tok_dtype, const float* g0, cons
 // Projection GEMM: y[m][n] = sum_k x[m][k] W[n][k], x bf16 [M][K], W packed (above).
 // Workgroup = 4 waves on one 16-column tile and one split-K range; the waves interleave its k-blocks,
 // then reduce their accumulators through LDS.  Each lane streams one 16-byte weight slot per k-block
-// (1 KiB coalesced per wave) and multiplies it by up to MT 16-row tiles of x.
+// (1 KiB coalesced per wave).  k_gemm takes one row tile (at most 16 rows); k_gemm_rows, below, more.
 // =====================================================================================================
 enum { EPI_QKV = 0, EPI_SWIGLU = 1, EPI_PARTIAL = 2 };
 
@@ -211,9 +211,9 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x4 s, int ro
   }
 }
 
-template <int MT, int EPI>
+template <int EPI>
 __global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
-  __shared__ f32x4 red[4][MT][WAVE];
+  __shared__ f32x4 red[4][WAVE];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int c = lane & 15, grp = lane >> 4;
   const int n_tiles = g.N / 16;
@@ -222,76 +222,48 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
   const int kbs = KB / g.ksplit;
   const int kb0 = ks * kbs, kb1 = kb0 + kbs;
   const uint4* __restrict__ wt = g.w + (int64_t)nt * KB * WAVE + lane;
-  const int n_mt = (g.M + 15) / 16;
-  for (int mg = 0; mg < n_mt; mg += MT) {
-    f32x4 acc[MT];
-    const uint16_t* xr[MT];
-    bool ok[MT];
-    float rsc[MT][4];  // row scales of this lane's epilogue rows, loaded before the weight stream
+  const bool ok = c < g.M;
+  const uint16_t* xr = g.x + (int64_t)(ok ? c : 0) * g.ldx + 8 * grp;
+  float rsc[4];  // row scales of this lane's epilogue rows, loaded before the weight stream
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-      const int row = (mg + mt) * 16 + c;
-      ok[mt] = row < g.M;
-      xr[mt] = g.x + (int64_t)(ok[mt] ? row : 0) * g.ldx + 8 * grp;
+  for (int i = 0; i < 4; ++i) rsc[i] = EPI != EPI_PARTIAL && g.rscale && 4 * grp + i < g.M ? g.rscale[4 * grp + i] : 1.f;
+  float2 cs[4];
+  if (wave == 0) load_rope<EPI>(g, 0, nt, c, grp, cs);
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  // Batches of U k-blocks of this wave: every weight block and x operand of the batch is loaded before the first
+  // MFMA, so U KiB of weights per wave are in flight (one at a time leaves the stream latency-bound).
+  constexpr int U = 8;
+  int kb = kb0 + wave;
+  for (; kb + 4 * (U - 1) < kb1; kb += 4 * U) {
+    uint4 wv[U], xv[U];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int er = (mg + mt) * 16 + 4 * grp + i;
-        rsc[mt][i] = EPI != EPI_PARTIAL && g.rscale && er < g.M ? g.rscale[er] : 1.f;
-      }
-    }
-    float2 cs[(MT + 3) / 4][4];
+    for (int u = 0; u < U; ++u) wv[u] = ld_global(wt + (int64_t)(kb + 4 * u) * WAVE);
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-      if (mt % 4 == wave) load_rope<EPI>(g, (mg + mt) * 16, nt, c, grp, cs[mt / 4]);
-    // Batches of U k-blocks of this wave: every weight block and x operand of the batch is loaded before the first
-    // MFMA, so U KiB of weights per wave are in flight (one at a time leaves the stream latency-bound).
-    constexpr int U = MT <= 1 ? 8 : (MT <= 2 ? 6 : (MT <= 4 ? 4 : 2));
-    int kb = kb0 + wave;
-    for (; kb + 4 * (U - 1) < kb1; kb += 4 * U) {
-      uint4 wv[U], xv[U][MT];
+    for (int u = 0; u < U; ++u) xv[u] = ok ? *reinterpret_cast<const uint4*>(xr + (kb + 4 * u) * 32) : make_uint4(0, 0, 0, 0);
 #pragma unroll
-      for (int u = 0; u < U; ++u) wv[u] = ld_global(wt + (int64_t)(kb + 4 * u) * WAVE);
+    for (int u = 0; u < U; ++u) acc = mfma_bf16(xv[u], wv[u], acc);
+  }
+  if (kb < kb1) {
+    // the last, partial batch: its k-blocks loaded together too (the missing ones as zeros), so a short split-K
+    // range costs one load latency instead of one per k-block
+    uint4 wv[U], xv[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-          xv[u][mt] = ok[mt] ? *reinterpret_cast<const uint4*>(xr[mt] + (kb + 4 * u) * 32) : make_uint4(0, 0, 0, 0);
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[mt] = mfma_bf16(xv[u][mt], wv[u], acc[mt]);
-    }
-    if (kb < kb1) {
-      // the last, partial batch: its k-blocks loaded together too (the missing ones as zeros), so a short split-K
-      // range costs one load latency instead of one per k-block
-      uint4 wv[U], xv[U][MT];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const bool in = kb + 4 * u < kb1;
-        wv[u] = in ? ld_global(wt + (int64_t)(kb + 4 * u) * WAVE) : make_uint4(0, 0, 0, 0);
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-          xv[u][mt] = in && ok[mt] ? *reinterpret_cast<const uint4*>(xr[mt] + (kb + 4 * u) * 32) : make_uint4(0, 0, 0, 0);
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (kb + 4 * u < kb1)
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt) acc[mt] = mfma_bf16(xv[u][mt], wv[u], acc[mt]);
+    for (int u = 0; u < U; ++u) {
+      const bool in = kb + 4 * u < kb1;
+      wv[u] = in ? ld_global(wt + (int64_t)(kb + 4 * u) * WAVE) : make_uint4(0, 0, 0, 0);
+      xv[u] = in && ok ? *reinterpret_cast<const uint4*>(xr + (kb + 4 * u) * 32) : make_uint4(0, 0, 0, 0);
     }
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) red[wave][mt][lane] = acc[mt];
-    __syncthreads();
+    for (int u = 0; u < U; ++u)
+      if (kb + 4 * u < kb1) acc = mfma_bf16(xv[u], wv[u], acc);
+  }
+  red[wave][lane] = acc;
+  __syncthreads();
+  if (wave == 0) {
+    f32x4 s = red[0][lane] + red[1][lane] + red[2][lane] + red[3][lane];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      if (mt % 4 != wave) continue;
-      f32x4 s = red[0][mt][lane] + red[1][mt][lane] + red[2][mt][lane] + red[3][mt][lane];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) s[i] *= rsc[mt][i];
-      gemm_epilogue<EPI>(g, s, (mg + mt) * 16, nt, ks, c, grp, cs[mt / 4]);
-    }
-    __syncthreads();
+    for (int i = 0; i < 4; ++i) s[i] *= rsc[i];
+    gemm_epilogue<EPI>(g, s, 0, nt, ks, c, grp, cs);
   }
 }
 
@@ -471,11 +443,12 @@ static hipError_t launch_rows(const GemmArgs& g, hipStream_t s) {
 // What a projection's workgroups cost a CU, in 128-byte lines weighted by how long each keeps its place: a CU has about
 // 64 lines in flight (read requests x their mean latency over the CUs' cycles came to 43 to 67 in these kernels),
 // whatever the depth of the ring, so its time goes with the lines it loads: 8 per column tile and k-block for the
-// weights, 8 per row tile for the rows, in whole rounds of 256 workgroups.  A line of weights from memory takes about
+// weights, 8 per row tile for the rows, in whole rounds of CUS workgroups.  A line of weights from memory takes about
 // three times as long as one of the rows from L2; with several row blocks all but one find the weights in L2.
+constexpr int CUS = 256;  // compute units of an MI355X, as one device
 static int64_t cu_cost(int n_rb, int mt, int tiles, int KB, int ksplit, int tpw) {
   const int64_t wgs = (int64_t)((tiles + tpw - 1) / tpw) * ksplit * n_rb;
-  return (wgs + 255) / 256 * (8 * tpw * (n_rb > 1 ? 1 : 3) + 8 * mt) * ((KB + ksplit - 1) / ksplit);
+  return (wgs + CUS - 1) / CUS * (8 * tpw * (n_rb > 1 ? 1 : 3) + 8 * mt) * ((KB + ksplit - 1) / ksplit);
 }
 // Column tiles per workgroup: the cheapest of what the kernels are built for.
 static int pick_tiles(int n_mt, int tiles, int KB, int ksplit) {
@@ -498,7 +471,7 @@ int gemm_split(int M, int N, int K) {
   if (n_rb == 1) return best;
   int64_t cost = INT64_MAX;
   for (int ks = 1; ks <= 8 && ks <= KB; ks *= 2) {
-    const int64_t c = cu_cost(n_rb, 8, tiles, KB, ks, pick_tiles(n_mt, tiles, KB, ks)) + (int64_t)ks * M * N * 8 / 128 / 256 * 2;
+    const int64_t c = cu_cost(n_rb, 8, tiles, KB, ks, pick_tiles(n_mt, tiles, KB, ks)) + (int64_t)ks * M * N * 8 / 128 / CUS * 2;
     if (c < cost) {
       best = ks;
       cost = c;
@@ -508,10 +481,44 @@ int gemm_split(int M, int N, int K) {
 }
 
 // More than 16 rows over a K range that LDS holds whole: row tiles (2 to 5) and column tiles of a workgroup, by its rounds of
-// 256 workgroups times its row tiles and a third of its column tiles (the rows pass through LDS, the weights stream by
+// CUS workgroups times its row tiles and a third of its column tiles (the rows pass through LDS, the weights stream by
 // them).  Of the pairs below, at 74 to 400 rows of the expert, the rule picks the fastest or one within 0.5 us of it, with
 // two exceptions of 1 us.  us against row tiles of 5 and 8 weighed as much as column tiles: q/k/v of 74 rows 9.9 -> 8.2, of
 // 400 rows 23.0 -> 18.6; gate/up of 160 rows 7.6 -> 5.4, O and down 6.2 -> 5.6.
+// The rule never picks the other pairs (evaluated for every count of row tiles to 400 and some to 5,000, up to 128 heads,
+// widths to 8,192, FFNs to 16,384).
+template <int EPI>
+constexpr bool short_pair(int mt, int t) {
+  return mt == 2 || (EPI == EPI_PARTIAL ? t > 1 && (t != 3 || mt == 3) : t >= (mt < 4 ? mt : 4));
+}
+
+template <int MT, int EPI>
+static hipError_t launch_short(const GemmArgs& g, int tpw, hipStream_t s) {
+  auto pair = [&](auto t) {
+    constexpr int T = decltype(t)::value;
+    if constexpr (!short_pair<EPI>(MT, T))
+      return hipErrorInvalidValue;  // not among the rule's pairs
+    else if constexpr (T <= 4)
+      return launch_rows<MT, 1, 4, 16, EPI, T, true>(g, s);
+    else if constexpr (T == 6)
+      return launch_rows<MT, 1, 4, 8, EPI, 6, true>(g, s);
+    else if constexpr (T == 8)
+      return launch_rows<MT, 2, 4, 8, EPI, 4, true>(g, s);
+    else
+      return launch_rows<MT, 3, 4, 4, EPI, T / 3, true>(g, s);
+  };
+  switch (tpw) {
+    case 1: return pair(std::integral_constant<int, 1>());
+    case 2: return pair(std::integral_constant<int, 2>());
+    case 3: return pair(std::integral_constant<int, 3>());
+    case 4: return pair(std::integral_constant<int, 4>());
+    case 6: return pair(std::integral_constant<int, 6>());
+    case 8: return pair(std::integral_constant<int, 8>());
+    case 12: return pair(std::integral_constant<int, 12>());
+    default: return pair(std::integral_constant<int, 24>());
+  }
+}
+
 template <int EPI>
 static hipError_t gemm_short(const GemmArgs& g, hipStream_t s) {
   const int n_mt = (g.M + 15) / 16, tiles = g.N / 16;
@@ -520,36 +527,21 @@ static hipError_t gemm_short(const GemmArgs& g, hipStream_t s) {
   int64_t best = INT64_MAX;
   for (int m : opt_mt)
     for (int t : opt_t) {
+      if (!short_pair<EPI>(m, t)) continue;
       const int64_t wgs = (int64_t)((tiles + t - 1) / t) * g.ksplit * ((n_mt + m - 1) / m);
-      const int64_t cost = (wgs + 255) / 256 * (3 * m + t);
+      const int64_t cost = (wgs + CUS - 1) / CUS * (3 * m + t);
       if (cost <= best) {
         best = cost;
         mt = m;
         tpw = t;
       }
     }
-#define FSX_SHORT(M)                                                 \
-  switch (tpw) {                                                     \
-    case 1: return launch_rows<M, 1, 4, 16, EPI, 1, true>(g, s);     \
-    case 2: return launch_rows<M, 1, 4, 16, EPI, 2, true>(g, s);     \
-    case 3: return launch_rows<M, 1, 4, 16, EPI, 3, true>(g, s);     \
-    case 4: return launch_rows<M, 1, 4, 16, EPI, 4, true>(g, s);     \
-    case 6: return launch_rows<M, 1, 4, 8, EPI, 6, true>(g, s);      \
-    case 8: return launch_rows<M, 2, 4, 8, EPI, 4, true>(g, s);      \
-    case 12: return launch_rows<M, 3, 4, 4, EPI, 4, true>(g, s);     \
-    default: return launch_rows<M, 3, 4, 4, EPI, 8, true>(g, s);     \
+  switch (mt) {
+    case 2: return launch_short<2, EPI>(g, tpw, s);
+    case 3: return launch_short<3, EPI>(g, tpw, s);
+    case 4: return launch_short<4, EPI>(g, tpw, s);
+    default: return launch_short<5, EPI>(g, tpw, s);
   }
-  if (mt == 2) {
-    FSX_SHORT(2)
-  }
-  if (mt == 3) {
-    FSX_SHORT(3)
-  }
-  if (mt == 4) {
-    FSX_SHORT(4)
-  }
-  FSX_SHORT(5)
-#undef FSX_SHORT
 }
 
 template <int EPI>
@@ -558,7 +550,7 @@ static hipError_t gemm_dispatch(const GemmArgs& g, hipStream_t s) {
   if (n_mt == 1) {
     // weights alone: a workgroup per column tile, its waves splitting K (gate/up of the backbone 35 us, 5.1 TB/s; the
     // kernel for many rows 39)
-    hipLaunchKernelGGL((k_gemm<1, EPI>), dim3((unsigned)(tiles * g.ksplit)), dim3(256), 0, s, g);
+    hipLaunchKernelGGL((k_gemm<EPI>), dim3((unsigned)(tiles * g.ksplit)), dim3(256), 0, s, g);
     return hipGetLastError();
   }
   if (g.K / 32 <= SHORT_CHUNKS * 4 * g.ksplit) return gemm_short<EPI>(g, s);
@@ -634,9 +626,9 @@ hipError_t launch_gemm_down(const FastWeights& w, const TickParams& tp, const Di
 
 // =====================================================================================================
 // Split-K joint attention (Eq. (1)): one wave = one work item = (agent, head, chunk of cached rows; see
-// attn_device.h) of agents with one query tile, an agent's last chunk followed by the new tokens' own rows.  The wave that finishes last among the
-// chunks of an (agent, head) merges their states in chunk order, so no launch does; an agent of one chunk
-// writes its output at once.  Partial states cross through device-scope stores and loads, counted by a relaxed
+// attn_device.h) of agents with one query tile, an agent's last chunk followed by the new tokens' own rows.  The wave that
+// finishes last among the chunks of an (agent, head) merges their states in chunk order, so no launch does; an agent of one
+// chunk writes its output at once.  Partial states cross through device-scope stores and loads, counted by a relaxed
 // device-scope atomic that the last wave resets (as k_reduce_chunks counts a row's chunks).
 // =====================================================================================================
 struct AttnArgs {
@@ -644,8 +636,8 @@ struct AttnArgs {
   const float* q;
   const uint16_t* kself;
   const uint16_t* vself;
-  float* att_o;        // [item][16][Dh] partial outputs (rows of valid queries only)
-  float* att_ml;       // [item][16][2]
+  float* att_o;        // [item][2048] partial outputs and
+  float* att_ml;       // [item][32] their maxima and sums, laid out by store_state
   uint32_t* acnt;      // [B * H * n_tt] chunks finished (zero between launches)
   uint16_t* attn_out;  // [M][A] bf16
   int H, Dh, A;

@@ -24,7 +24,7 @@ struct TickParams {
   int64_t pos[FSX_MAX_BATCH];                 // rotary position of token 0
   int64_t start[FSX_MAX_BATCH];               // ring slot of the oldest valid row
   int32_t len[FSX_MAX_BATCH];                 // valid cache rows
-  int32_t chunk_prefix[FSX_MAX_BATCH + 1];    // per-phase path: chunks before agent b (max(1, ceil(len / chunk_rows)) each)
+  int32_t chunk_prefix[FSX_MAX_BATCH + 1];    // per-phase path: chunks before agent b (plan_chunks; at least one each)
   // tick kernel attention: agents in the order order[0..B-1]; the k-th weighs seg_w[k] work tiles per head
   // (its 32-row cache tiles, then the 32-row tiles of the expert's own rows), seg_p[k] = seg_w[0] + ... +
   // seg_w[k-1]; partial-state slots of XCD X
@@ -88,8 +88,10 @@ struct Workspace {
   uint16_t* attn;    // [M][A] bf16 attention output
   uint16_t* z;       // [M][F] bf16 SwiGLU output
   float* part;       // [ksplit][M][d] split-K partial sums
-  float* att_o;      // [items][16][Dh] unnormalised partial attention outputs
-  float* att_ml;     // [items][16][2] running max (log2 units) and sum
+  // partial attention states, 16 * Dh and 32 floats per item: unnormalised outputs, running maxima (log2 units) and sums (the
+  // tick kernel: [16][Dh] and [16][2]; the phases: in the order of store_state)
+  float* att_o;
+  float* att_ml;
   float* rope;       // [M][Dh/2][2] cos, sin
   float* ss;         // [M][d/512] per-chunk sums of squares (wide rows)
   float* rs;         // [M] RMSNorm scale of each row (wide rows)
