@@ -62,6 +62,35 @@ def test_noalloc_tick_matches_forward_on_two_calls(flags):
     ex.close()
 
 
+def test_captured_tick_of_many_rows_replays_as_eager_ones():
+    """A tick that runs as a launch per phase, captured into a graph: each replay on new tokens gives the eager result bit for
+    bit, with eager ticks of the same array and synchronisations between the replays."""
+    wl = wl_of(304, lengths=(600, 37, 250), n_frame=30)
+    say("case captured tick of 120 rows")
+    model = Model(wl)
+    ex = model.create()
+    cache = Cache(wl, starts=(5, 0, 300))
+    toks = [tokens_for(wl.replace(wid=304 + i))[1] for i in range(3)]
+    want = [noalloc_forward(ex, cache, t, wl.batch, wl.n_frame_tokens) for t in toks]
+    assert not np.array_equal(want[0][0], want[1][0])
+    tok = toks[0].clone()
+    wp = torch.zeros((wl.batch, wl.n_out), device="cuda")
+    hid = torch.zeros((wl.n_layers, wl.batch, wl.seq, wl.d_model), device="cuda")
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        fsx.expert_forward_noalloc(ex, cache.desc, tok, wl.batch, wl.n_frame_tokens, wp, hid)
+    for i in (1, 0, 2, 2, 1):
+        tok.copy_(toks[i])
+        wp.fill_(float("nan"))
+        hid.fill_(float("nan"))
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(wp.cpu().numpy(), want[i][0]) and np.array_equal(hid.cpu().numpy(), want[i][1]), f"token set {i}"
+        again = noalloc_forward(ex, cache, toks[0], wl.batch, wl.n_frame_tokens)  # the array's contents change between replays
+        assert np.array_equal(again[0], want[0][0])
+    ex.close()
+
+
 def test_noalloc_refuses_what_does_not_fit():
     # full widths, one layer, 64 agents of 10 tokens: the workspace exceeds the static array
     wl = synth.Workload(name="noalloc_big", wid=302, n_layers=1, d_model=512, n_heads=32, head_dim=128, d_ffn=2048,
