@@ -127,7 +127,7 @@ def summarize_trace(d: str, workload: str, bench_line: str, command: str, name: 
     directory."""
     rows = _csv_rows(d, "kernel_stats.csv")
     line = json.loads(open(bench_line).read().strip().splitlines()[-1])
-    title = f"tick kernel, workload `{workload}`" if not name else f"`{name}` (bench.py run of workload `{workload}`)"
+    title = f"tick, workload `{workload}`" if not name else f"`{name}` (bench.py run of workload `{workload}`)"
     out = [f"# Kernel trace: {title}", "", "Command (from the repository root, on one MI355X):",
            "", "```", command, "```", "", "| kernel | calls | total ms | avg µs | min µs | max µs |",
            "|---|---|---|---|---|---|"]
@@ -145,29 +145,44 @@ def summarize_trace(d: str, workload: str, bench_line: str, command: str, name: 
     print(path)
 
 
+TICK_KERNELS = ("k_tick", "k_embed", "k_gemm", "k_attention", "k_reduce", "k_head", "k_query_head")
+
+
+def tick_counter(d: str, counter: str):
+    """(value per tick, ticks) of one counter in a rocprofv3 output directory, over the kernels of a tick: one persistent
+    launch, or the launches per phase, of which the embedding runs once a tick."""
+    rows = [(r["Kernel_Name"], float(r["Counter_Value"])) for r in _csv_rows(d, "counter_collection.csv")
+            if r["Counter_Name"] == counter and any(k in r["Kernel_Name"] for k in TICK_KERNELS)]
+    ticks = sum("k_tick" in n or "k_embed" in n for n, _ in rows)
+    return (sum(v for _, v in rows) / ticks, ticks) if ticks else (None, 0)
+
+
 def summarize_traffic(dirs, workload: str, copy_bytes: int, commands, dram: bool = False):
-    """profiles/traffic_<workload>.json: HBM bytes per tick-kernel launch from two counters, each scaled by what the
+    """profiles/traffic_<workload>.json: HBM bytes per tick from two counters, each scaled by what the
     same counter reads for a plain device copy of copy_bytes.  Default: FETCH_SIZE / WRITE_SIZE (L2 <-> fabric
     traffic, Infinity Cache hits included); with dram: TCC_EA0_RDREQ_DRAM_sum / TCC_EA0_WRREQ_DRAM_sum (requests
     the L2 sends towards DRAM).  dirs: read counter of the tick, write counter of the tick, then the same two for
     the copy.  Both sets live in the same file; each is kept only while the kernel sources match."""
-    def mean_counter(d, counter, pick):
+    def copy_counter(d, counter):
         vals = [float(r["Counter_Value"]) for r in _csv_rows(d, "counter_collection.csv")
-                if r["Counter_Name"] == counter and pick(r["Kernel_Name"])]
+                if r["Counter_Name"] == counter and ("copy" in r["Kernel_Name"].lower() or
+                                                     "elementwise" in r["Kernel_Name"].lower())]
         if not vals:
             raise SystemExit(f"no {counter} rows in {d}")
-        return vals
+        return max(vals)
+
+    def per_tick(d, counter):
+        value, ticks = tick_counter(d, counter)
+        if not ticks:
+            raise SystemExit(f"no {counter} rows in {d}")
+        return value, ticks
 
     rd, wr = ("TCC_EA0_RDREQ_DRAM_sum", "TCC_EA0_WRREQ_DRAM_sum") if dram else ("FETCH_SIZE", "WRITE_SIZE")
-    tick = lambda n: "k_tick" in n
-    copyk = lambda n: "copy" in n.lower() or "elementwise" in n.lower()
-    f_tick = mean_counter(dirs[0], rd, tick)
-    w_tick = mean_counter(dirs[1], wr, tick)
-    f_copy = max(mean_counter(dirs[2], rd, copyk))
-    w_copy = max(mean_counter(dirs[3], wr, copyk))
+    f_tick, f_n = per_tick(dirs[0], rd)
+    w_tick, w_n = per_tick(dirs[1], wr)
+    f_copy, w_copy = copy_counter(dirs[2], rd), copy_counter(dirs[3], wr)
     kf, kw = copy_bytes / f_copy, copy_bytes / w_copy  # bytes per counter unit
-    fetch = sum(f_tick) / len(f_tick) * kf
-    write = sum(w_tick) / len(w_tick) * kw
+    fetch, write = f_tick * kf, w_tick * kw
     path = os.path.join(ROOT, "profiles", f"traffic_{workload}.json")
     d = {}
     if os.path.exists(path):
@@ -181,7 +196,7 @@ def summarize_traffic(dirs, workload: str, copy_bytes: int, commands, dram: bool
               f"{pre}calibration": {"copy_bytes": copy_bytes, "read_counter": rd, "write_counter": wr,
                                     "copy_read_count": f_copy, "copy_write_count": w_copy,
                                     "bytes_per_read_unit": kf, "bytes_per_write_unit": kw},
-              f"{pre}dispatches": {"read": len(f_tick), "write": len(w_tick)}, f"{pre}commands": commands})
+              f"{pre}ticks": {"read": f_n, "write": w_n}, f"{pre}commands": commands})
     json.dump(d, open(path, "w"), indent=1)
     print(path, json.dumps({k: v for k, v in d.items() if k.endswith("bytes_per_launch")}))
 
@@ -191,25 +206,26 @@ INSTR_COUNTERS = ("SQ_INSTS_VALU", "SQ_INSTS_MFMA", "SQ_INSTS_LDS", "SQ_INSTS_SA
 
 
 def summarize_counters(dirs, workloads, commands):
-    """profiles/instructions_tick.md: instruction counts of one tick-kernel launch per workload (wave-level
-    instructions summed over the device), LDS bank-conflict cycles and the MFMA busy fraction, from rocprofv3 --pmc
+    """profiles/instructions_tick.md: instruction counts of one tick per workload (wave-level instructions
+    summed over the device and the tick's launches), LDS bank-conflict cycles and the MFMA busy fraction, from rocprofv3 --pmc
     runs (dirs: for each workload in turn, one directory per pass)."""
     per = len(dirs) // len(workloads)
-    out = ["# Instruction mix of the tick kernel", "",
-           "One tick-kernel launch per workload, counters summed over the device and averaged over the profiled "
-           "launches: wave-level instructions by kind, LDS bank-conflict cycles, and the busy cycles of the MFMA "
+    out = ["# Instruction mix of a tick", "",
+           "One tick per workload, counters summed over the device and the tick's launches and averaged over the profiled "
+           "ticks: wave-level instructions by kind, LDS bank-conflict cycles, and the busy cycles of the MFMA "
            "units against those of the shader sequencers (SQ_VALU_MFMA_BUSY_CYCLES / SQ_BUSY_CYCLES; the counters "
-           "count in different units per block, so the ratio compares launches, not an absolute utilisation).", "",
+           "count in different units per block, so the ratio compares ticks, not an absolute utilisation).", "",
            "Commands (from the repository root, on one MI355X, one pass each):", "", "```"] + list(commands) + \
           ["```", "", "| workload | " + " | ".join(c.replace("SQ_", "") for c in INSTR_COUNTERS) + " |",
            "|---|" + "---:|" * len(INSTR_COUNTERS)]
     for i, w in enumerate(workloads):
         vals = {}
         for d in dirs[i * per:(i + 1) * per]:
-            for r in _csv_rows(d, "counter_collection.csv"):
-                if "k_tick" in r["Kernel_Name"]:
-                    vals.setdefault(r["Counter_Name"], []).append(float(r["Counter_Value"]))
-        cells = [f"{sum(vals[c]) / len(vals[c]):,.0f}" if c in vals else "–" for c in INSTR_COUNTERS]
+            for c in INSTR_COUNTERS:
+                value, ticks = tick_counter(d, c)
+                if ticks:
+                    vals[c] = value
+        cells = [f"{vals[c]:,.0f}" if c in vals else "–" for c in INSTR_COUNTERS]
         out.append(f"| `{w}` | " + " | ".join(cells) + " |")
     path = os.path.join(ROOT, "profiles", "instructions_tick.md")
     open(path, "w").write("\n".join(out) + "\n")
@@ -625,8 +641,8 @@ def run_sweep(steps: int, warmup: int, out_md: str, command: str, cache_dtype: s
     out = ["# Tick time across cache lengths and agent counts", "",
            "Full-size expert (32 layers, width 512, 32 heads x 128, SwiGLU 2048, 10 expert tokens), bf16 weights, "
            f"{'fp8 (E4M3, a scale per agent, layer and head for K and for V)' if cache_dtype == 'fp8' else 'bf16'} cache, no frame tokens, seeded "
-           "synthetic inputs; one persistent tick-kernel launch per tick, "
-           f"{steps} back-to-back launches timed with HIP events after {warmup} warm-up launches. `frac` is the "
+           "synthetic inputs; each tick in the form its rows take (one persistent launch, or a launch per phase), "
+           f"{steps} back-to-back ticks timed with HIP events after {warmup} warm-up ticks. `frac` is the "
            "algorithmic bytes (weights once, every cached K/V row once) per tick over 8 TB/s.", "",
            f"Command: `{command}`", "",
            "| agents | cache rows per agent | µs/tick | agent-ticks/s | algorithmic MB | GB/s | frac |",
@@ -650,7 +666,7 @@ def main():
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-hbm-probe", action="store_true")
     ap.add_argument("--no-backbone", action="store_true", help="skip the backbone's incremental forward")
-    ap.add_argument("--multi-launch", action="store_true", help="one launch per phase instead of the tick kernel")
+    ap.add_argument("--multi-launch", action="store_true", help="a launch per phase for every workload, whatever its rows")
     ap.add_argument("--copy-calibration", type=int, default=0, metavar="BYTES")
     ap.add_argument("--summarize-trace", metavar="DIR")
     ap.add_argument("--bench-line", metavar="FILE")
@@ -751,7 +767,7 @@ def main():
         "config": {"workload": wl.name, "agents": wl.batch, "cache_rows": list(wl.lengths)[:8],
                    "layers": wl.n_layers, "d_model": wl.d_model, "heads": wl.n_heads, "head_dim": wl.head_dim,
                    "d_ffn": wl.d_ffn, "expert_tokens": wl.n_expert_tokens, "frame_tokens": wl.n_frame_tokens,
-                   "launch": "multi" if args.multi_launch else "tick-kernel"},
+                   "launch": "per-phase" if args.multi_launch else "by rows"},
         "roofline": {"bound": "hbm", "achieved": h["achieved_gbs"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": h["frac"], "traffic": h["traffic"], "algorithmic_bytes_per_launch": h["algorithmic_bytes"]},
         "workloads": results,

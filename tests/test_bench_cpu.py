@@ -69,6 +69,19 @@ def test_counter_summary_averages_tick_launches_only(tmp_path, monkeypatch):
     assert "cmd a" in text and "cmd b" in text
 
 
+def test_counters_of_a_tick_of_several_launches_are_summed(tmp_path):
+    """Launches per phase: every kernel of the tick counts, and a tick is one embedding."""
+    rows = []
+    for scale in (1, 3):
+        for name, v in (("fsx::k_embed(void const*)", 1), ("void fsx::k_gemm_rows<2, 1, 4, 16, 0, 4, true>", 10),
+                        ("void fsx::k_attention_tiles<0>", 100), ("fsx::k_reduce_norm<false>", 1000), ("fsx::k_head", 10000)):
+            rows.append((name, "FETCH_SIZE", scale * v))
+    rows += [("fsx::k_append(fsx::AppendArgs)", "FETCH_SIZE", 7), ("fsx::k_pack", "FETCH_SIZE", 7)]
+    write_counters(tmp_path / "p", rows)
+    assert bench.tick_counter(str(tmp_path / "p"), "FETCH_SIZE") == (2 * 11111, 2)
+    assert bench.tick_counter(str(tmp_path / "p"), "WRITE_SIZE") == (None, 0)
+
+
 def test_traffic_summary_scales_by_the_copy_calibration(tmp_path, monkeypatch):
     real_hash = bench.source_hash()
     monkeypatch.setattr(bench, "ROOT", str(tmp_path))
