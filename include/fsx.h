@@ -181,7 +181,9 @@ int fsx_expert_create(const fsx_expert_cfg* cfg, const fsx_layer_weights* layers
  *   waypoints      DEVICE [batch][n_out] fp32 output
  *   hidden         DEVICE [n_layers][batch][S][d] fp32 output of every layer, or NULL
  * Uses only library-owned workspace; allocates nothing.  Calls that overlap on one
- * expert handle (e.g. from two streams) race on its workspace. */
+ * expert handle (e.g. from two streams) race on its workspace.
+ * A tick is one persistent launch (about 10 us of host time) or, where its rows of tokens
+ * are many, a launch per phase (7 per layer, about 3 us of host time each). */
 int fsx_expert_forward(fsx_expert* ex, const fsx_cache_desc* cache, const void* tokens, int32_t batch,
                        int32_t n_frame_tokens, float* waypoints, float* hidden, void* stream);
 
@@ -192,9 +194,10 @@ int fsx_expert_forward(fsx_expert* ex, const fsx_cache_desc* cache, const void* 
  * Each call first clears the part of that array that must start at zero, with a kernel on `stream`, so a call does
  * not depend on what an earlier call left there; calls that overlap on one device (other streams or threads) race
  * on the array and must be serialised by the caller.  Arguments and results as fsx_expert_forward.
- *   FSX_E_CAPACITY    the call's sizes need more than the array holds (the message gives the bytes needed;
- *                     e.g. 16 agents x 10 tokens or one agent x 74 tokens fit, 64 agents do not)
- *   FSX_E_UNSUPPORTED the handle does not run the persistent tick kernel (fp32 weights, FSX_FLAG_GENERIC,
+ *   FSX_E_CAPACITY    the tick kernel's workspace for the call's sizes is more than the array holds, whichever form
+ *                     the tick would take (the message gives the bytes; e.g. 16 agents x 10 tokens or one agent x 74
+ *                     tokens fit, 64 agents do not)
+ *   FSX_E_UNSUPPORTED the handle cannot run the persistent tick kernel (fp32 weights, FSX_FLAG_GENERIC,
  *                     FSX_FLAG_MULTI_LAUNCH, shapes outside the per-XCD split)
  * A tick that gives up on a wait writes NaN waypoints; fsx_expert_status does not report calls made here. */
 int fsx_expert_forward_noalloc(fsx_expert* ex, const fsx_cache_desc* cache, const void* tokens, int32_t batch,

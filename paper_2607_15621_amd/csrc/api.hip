@@ -431,12 +431,12 @@ static int validate_cache(const fsx_expert* ex, const fsx_cache_desc* c, int bat
 }
 
 // ------------------------------------------------------------------------------------------------------------
-// The entry point that allocates nothing keeps the tick kernel's workspace in `scratch`, a file-scope device array
-// of STATIC_SCRATCH_BYTES.  In host code `scratch` names a host-side stand-in, never a device address: the device
-// address is looked up once per device (hipGetSymbolAddress, with that device current) and only that pointer is
-// used.  Every call on a device shares its array; a call clears the part that must start at zero (flags, stamped
-// partial words, registration and status words) with a fill kernel on its stream, so calls are independent of the
-// previous contents, but calls that overlap on one device (two streams, two threads) race on the array.
+// The entry point that allocates nothing keeps a tick's workspace (the tick kernel's, or that of the launches per phase) in
+// `scratch`, a file-scope device array of STATIC_SCRATCH_BYTES.  In host code `scratch` names a host-side stand-in, never a
+// device address: the device address is looked up once per device (hipGetSymbolAddress, with that device current) and only
+// that pointer is used.  Every call on a device shares its array; a call clears the part that must start at zero (flags,
+// stamped partial words, registration and status words, chunk counters) with a fill kernel on its stream, so calls are
+// independent of the previous contents, but calls that overlap on one device (two streams, two threads) race on the array.
 constexpr size_t STATIC_SCRATCH_BYTES = (size_t)48 << 20;
 constexpr int STATIC_MAX_DEVICES = 64;
 static __device__ __align__(256) uint8_t scratch[STATIC_SCRATCH_BYTES];
@@ -676,8 +676,9 @@ static int forward_impl(fsx_expert* ex, const fsx_cache_desc* cache, const void*
   }
 
   if (use_static && !ex->tick)
-    return fail(FSX_E_UNSUPPORTED, "the allocation-free entry point runs the persistent tick kernel only (bf16 expert "
-                                   "whose heads and FFN columns fit the per-XCD split, no FSX_FLAG_MULTI_LAUNCH)");
+    return fail(FSX_E_UNSUPPORTED, "the allocation-free entry point needs a handle that can run the persistent tick kernel "
+                                   "(bf16 expert whose heads and FFN columns fit the per-XCD split, no "
+                                   "FSX_FLAG_MULTI_LAUNCH)");
   if (ex->path == 1) {
     HIP_TRY(generic_tick(ex->gw.data(), ex->final_norm, ex->head_w, ex->qhead, c.dtype, tokens, cv, tp, dm, ex->gws,
                          waypoints, hidden, s));
@@ -735,8 +736,8 @@ static int forward_impl(fsx_expert* ex, const fsx_cache_desc* cache, const void*
       // the workspace for this call's sizes, laid over the static array; epoch 1 on flags cleared by this call
       const size_t need = static_tick_layout(ex, tp, nullptr, a, &zoff);
       if (need > STATIC_SCRATCH_BYTES)
-        return fail(FSX_E_CAPACITY, "this call needs " + std::to_string(need) + " bytes of workspace; the static array "
-                                    "holds " + std::to_string(STATIC_SCRATCH_BYTES));
+        return fail(FSX_E_CAPACITY, "the tick kernel needs " + std::to_string(need) + " bytes of workspace for this call; "
+                                    "the static array holds " + std::to_string(STATIC_SCRATCH_BYTES));
       void* base = nullptr;
       rc = scratch_of(dev, &base);
       if (rc) return rc;
