@@ -1825,8 +1825,11 @@ __device__ __forceinline__ bool phase_oproj(const TickArgs& a, const TickParams&
 #pragma unroll
     for (int j = 0; j < IPF; ++j)
       if (it0 + j * n < total) load_unit_w(W.wo + (int64_t)((it0 + j * n) / R) * (A / 32) * WAVE, kb0, nkb, wg[j]);
-    if (first && nh > 0 &&
-        !wg_wait(a.f_attn + (int64_t)h0 * tp.n_tt * FPAD, tp.B * nh * tp.n_tt, st, a, L, nh * tp.n_tt, H * tp.n_tt))
+    // The attention output of X's heads.  An XCD without heads waits for the layer before: it may have no FFN columns either,
+    // and so nothing else to wait for, and would overwrite its words of that layer ahead of their readers, who then wait in
+    // vain for the older stamp (the last layer's pieces are out once every word of its two reductions has been read).
+    if (first && !wg_wait(nh > 0 ? a.f_attn + (int64_t)h0 * tp.n_tt * FPAD : a.f_out, nh > 0 ? tp.B * nh * tp.n_tt : nt * tp.rblk,
+                          nh > 0 ? st : stamp_of(a, l - 1, dm.n_layers), a, L, nh > 0 ? nh * tp.n_tt : 1 << 30, H * tp.n_tt))
       return false;
     if (first) TICK_SUB(l, 5);
 #pragma unroll 1

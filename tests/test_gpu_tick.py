@@ -55,6 +55,30 @@ def test_tick_kernel_and_per_phase_launches_match_oracle(n_frame):
     assert not np.array_equal(outs["tick"][1], outs["per-phase"][1]), "the two forms agree bitwise: one was compared with itself"
 
 
+# heads and FFN width that leave XCDs without work: no heads and no columns (1 head, 32 and 96 columns), no heads only, no
+# columns only; one, two and eight query tiles, one row block and several
+@pytest.mark.parametrize("n_heads,d_ffn,d_model,n_frame,batch", [(1, 32, 512, 0, 3), (2, 96, 128, 14, 2), (1, 96, 32, 0, 1),
+                                                               (2, 32, 352, 106, 4), (1, 512, 256, 0, 2), (8, 32, 256, 0, 2)])
+def test_xcds_without_heads_or_columns_match_oracle(n_heads, d_ffn, d_model, n_frame, batch):
+    """Six layers, so that an XCD with nothing to wait for could run ahead of the others' reductions."""
+    wl = small(140 + n_heads, lengths=tuple(33 * (b + 1) for b in range(batch)), n_frame=n_frame, n_layers=6, d_model=d_model,
+               n_heads=n_heads, d_ffn=d_ffn)
+    say(f"case idle XCDs: {n_heads} heads, {d_ffn} columns, width {d_model}, {batch} x {wl.seq} tokens")
+    model = Model(wl)
+    cache = Cache(wl, starts=(390,) * batch)
+    host_tok, tok = tokens_for(wl)
+    ex = model.create(flags=fsx.FLAG_TRACE)
+    for _ in range(3):
+        wp, hid = run_forward(ex, cache, tok, batch, n_frame, with_hidden=True)
+        fsx.expert_status(ex)
+    for b in range(batch):
+        ref, ref_hid = model.oracle_agent(host_tok[b], cache.oracle_rows(b), cache.desc.pos[b])
+        record(b, rel_err(wp[b], ref), TOL)
+        record(b, max(rel_err(hid[l, b], ref_hid[l]) for l in range(wl.n_layers)), TOL,
+               what="worst layer hidden, max|d| / max|ref|")
+    ex.close()
+
+
 @pytest.mark.parametrize("lengths", [(150,), (0,), (333,)])
 def test_single_agent_small_matches_oracle(lengths):
     """One agent, one query tile, 2 heads per XCD (one attention workgroup per head, no partial states), per-layer
