@@ -441,7 +441,7 @@ static hipError_t launch_rows(const GemmArgs& g, hipStream_t s) {
 }
 
 // What a projection's workgroups cost a CU, in 128-byte lines weighted by how long each keeps its place: a CU has about
-// 64 lines in flight (read requests x their mean latency over the CUs' cycles came to 43 to 67 in these kernels),
+// 64 lines in flight (read requests x their mean latency over the CUs' cycles come to 43 to 81 at the backbone's widths),
 // whatever the depth of the ring, so its time goes with the lines it loads: 8 per column tile and k-block for the
 // weights, 8 per row tile for the rows, in whole rounds of CUS workgroups.  A line of weights from memory takes about
 // three times as long as one of the rows from L2; with several row blocks all but one find the weights in L2.
