@@ -590,8 +590,7 @@ static void plan_chunks(const fsx_expert* ex, TickParams& tp, int64_t rows, bool
 // of 80, each as one more round of every phase, and streams the cache of an agent of many queries through one loader wave per
 // CU; a launch per phase costs about 3 us whatever the rows, and one wave per chunk streams long histories more slowly than
 // the kernel's rings.  us per tick, kernel and phases, of the full expert (32 layers of 32 heads); the other widths and
-// head counts measured (8 layers of 256 and 8 heads, 16 of 512 and 16, 4 of 128 and 4) keep within 4 % of the faster form
-// on the phases' side of the lines that bound it, their cached rows counted by heads.
+// head counts measured are 8 layers of 256 and 8 heads, 16 of 512 and 16, 4 of 128 and 4.
 //   agents of one shared cache: 80 rows of tokens 1,326 and 1,382, 120 rows 2,019 and 1,480, 400 rows 5,202 and 2,127; over
 //     16,000 rows 120 rows 8,450 and 4,149 (fp8 7,175 and 5,264).
 //   several query tiles per agent: 26 rows over 224 cached ones 1,228 and 1,218, over 4,000 1,684 and 1,530; 60 rows 1,503
@@ -602,28 +601,40 @@ static void plan_chunks(const fsx_expert* ex, TickParams& tp, int64_t rows, bool
 //     4,280; 120 rows over 16,000 2,932 and 2,627, over 64,000 5,928 and 6,325; 416 rows over 64,000 9,088 and 7,120, over
 //     256,000 20,780 and 21,880.  Three tiles and more, and bf16 rows: the phases at every length.
 //   one query tile per agent: 80 rows 1,523 and 1,543, 100 rows 1,885 and 1,700.  Beyond 96 rows the line lies at the length
-//     where the rounds of the chain that the phases save are used up by their slower streaming.  That is slowest where the
+//     where the rounds of the chain that the phases save are used up by their slower streaming.  That is slower where the
 //     attention's waves exceed one round of eight per CU, which equal shares of 16, 32 or 64 agents do not: 150 rows over
 //     15,000 bf16 rows 3,334 and 2,794, over 30,000 4,727 and 4,966, over 120,000 12,307 and 14,365; fp8 over 30,000 3,581
 //     and 3,397, over 60,000 4,923 and 5,290, over 240,000 12,457 and 15,916; 320 rows in uneven histories over 32,512 bf16
 //     rows 6,248 and 5,770, over 65,008 8,921 and 9,199, fp8 6,753 and 6,318, over 130,000 9,359 and 10,295; 640 rows (40
-//     agents) over 160,000 18,137 and 19,486, fp8 11,898 and 12,665.  In one round: 160 rows over 192,000 bf16 rows 17,978
-//     and 17,677, fp8 over 64,000 4,967 and 4,933, over 256,000 13,079 and 14,360; 320 rows over 256,000 fp8 rows 14,162 and
-//     14,933.
+//     agents) over 160,000 18,137 and 19,486, fp8 11,898 and 12,665;
+//   slower still with more waves than the twelve per CU that fit, which start when others end: 480 rows (48 agents, 3,072
+//     waves) over 69,000 bf16 rows 11,244 and 9,890, 490 rows (49 agents, 3,136 waves) over 70,500 11,667 and 11,860, over
+//     49,000 9,971 and 9,088; 637 rows (49 agents) over 34,300 8,156 and 7,584, over 49,000 9,312 and 9,595;
+//   in one round: 160 rows over 192,000 bf16 rows 17,978 and 17,677, fp8 over 64,000 4,967 and 4,933, over 256,000 13,079
+//     and 14,360; 320 rows over 256,000 fp8 rows 14,162 and 14,933;
+//   narrower layers, kernel over phases, cached rows by heads: 16 heads 310 uneven rows over 30,600 bf16 rows 1.01, over
+//     61,200 0.92 (fp8 1.09, 0.96), 480 rows over 95,500 1.10 (fp8 1.22); 8 heads and width 256 310 rows over 15,300 1.13,
+//     over 30,600 0.94 (fp8 1.14, 0.94).
 static bool phases_faster(const TickParams& tp, const Dims& dm, int64_t rows, bool fp8) {
   const int64_t load = rows * dm.H / 32;  // cached rows of 32 heads
   if (tp.n_tt > 1) {
     if (tp.M <= 32 && rows < 1024) return false;
     if (tp.n_tt > 2 && tp.M <= 48 && dm.H > 16 && rows < 224) return false;
     if (!fp8 || tp.n_tt > 2 || tp.att_shared) return true;
-    return load <= (tp.M <= 48 ? 12000 : (tp.M <= 80 ? 24000 : (tp.M <= 320 ? 40000 : 150000)));
+    return load <= (tp.M <= 48 ? 12000 : (tp.M <= 80 ? 24000 : (tp.M <= 320 ? 40000 : 120000)));
   }
   if (tp.M <= 96) return false;
   if (tp.att_shared) return true;
   if (tp.M <= 144) return rows <= 8192;
-  const int64_t blocks = (tp.M + 79) / 80;
+  const int blocks = (tp.M + 79) / 80;
   if (tp.n_items <= ATT_WAVES) return !fp8 || load <= 30000 * blocks;
-  return load <= std::min<int64_t>((fp8 ? 32000 : 16000) * (blocks - 1), 110000);
+  // tenths of the round that a second block adds: what 2, 3, .. 8 blocks cost the kernel's chain (2, 4 and 8 blocks divide the
+  // 32 workgroups of an XCD, which then stage one block each); the cached rows that use up one round, less where the layers
+  // are narrow and the round is short
+  static constexpr int rounds[] = {10, 22, 18, 50, 65, 65, 50};
+  const int64_t per_round = fp8 ? (dm.H >= 32 ? 28000 : (dm.H >= 16 ? 20000 : 11000)) : (dm.H >= 16 ? 16000 : 11000);
+  const int64_t limit = per_round * rounds[std::min(blocks, 8) - 2] / 10;
+  return load <= (tp.n_items <= ATT_WAVES * 3 / 2 ? limit : limit * 3 / 5);
 }
 
 static int forward_impl(fsx_expert* ex, const fsx_cache_desc* cache, const void* tokens, int32_t batch,

@@ -129,7 +129,7 @@ def test_route_of_a_tick_by_its_rows(batch, frame, rows, shared, phases):
 
 # agents, frame tokens, cached rows of each, fp8 cache, whether a launch per phase is the faster form: 32 heads, histories on
 # both sides of where the kernel's streaming makes up for its rounds
-LONG_ROUTES = [(15, 0, 1066, False, True), (15, 0, 1067, False, False), (15, 0, 2133, True, True), (15, 0, 2134, True, False),
+LONG_ROUTES = [(15, 0, 1066, False, True), (15, 0, 1067, False, False), (15, 0, 1866, True, True), (15, 0, 1867, True, False),
                (16, 0, 3751, False, True), (16, 0, 3750, True, True), (16, 0, 3751, True, False),
                (1, 22, 12000, True, True), (1, 22, 12001, True, False), (1, 22, 12001, False, True),
                (1, 30, 223, False, False), (1, 30, 224, False, True)]
